@@ -5,10 +5,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 
 #include "basis_ct.h"
 #include "common.h"
+#include "ops.h"
 
 namespace dgmf {
 
@@ -114,6 +116,19 @@ __device__ __forceinline__ decltype(auto) conv_pick(const ConvTab<N, Q, T>& ct, 
   constexpr ConvTab<N, Q, T> t##_ct =                               \
       sizeof(T) == 4 ? conv_tab_ct<N, Q, T>() : ConvTab<N, Q, T>{}; \
   const auto& t = conv_pick<N, Q, T>(t##_ct, tab)
+
+// Whether the plan's tables are the kernels' compile-time ones.
+template <int N, int Q>
+bool conv_tables_match(const ConvPlan& P) {
+  constexpr ct::Tables<N, Q> C{};
+  for (int q = 0; q < Q; ++q) {
+    if (std::fabs(C.w[q] - P.w[q]) > 1e-13) return false;
+    for (int a = 0; a < N; ++a)
+      if (std::fabs(C.S[q][a] - P.S[q * N + a]) > 1e-13 || std::fabs(C.G[q][a] - P.G[q * N + a]) > 1e-11)
+        return false;
+  }
+  return true;
+}
 
 template <typename T>
 struct ConvScal {

@@ -65,6 +65,8 @@ struct ConvPlan {
 };
 
 hipError_t launch_convective(const ConvPlan& P, bool f32, const void* u, void* r, hipStream_t s);
+// degrees 4..11, called by launch_convective
+hipError_t launch_convective_split(const ConvPlan& P, bool f32, const void* u, void* r, hipStream_t s);
 hipError_t launch_convective_vjp(const ConvPlan& P, bool f32, const void* u, const void* w,
                                  void* g, hipStream_t s);
 

@@ -159,6 +159,25 @@ def test_input_alignment(k, dtype):
     assert rel_err(ya.double().cpu().numpy(), convective_apply(u, k, msh)) < tol
 
 
+@pytest.mark.parametrize("n_el", [(1, 1, 1), (2, 1, 3), (1, 4, 2)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("k", list(range(4, 12)))
+def test_one_component_per_thread_kernel(k, dtype, n_el):
+    """k >= 4 runs one thread per pencil and component: every degree and type
+    on meshes where an element is its own neighbour (1 per direction), sees
+    the same neighbour on both sides (2), or has distinct ones (3, 4).
+    Tolerances of this file: FP64 1e-12, FP32 1e-5."""
+    length = (1.0, 2.0, 0.5)
+    msh = M.Mesh(n_el, length)
+    u = inputs.uniform((3, msh.N, (k + 1) ** 3), seed=1400 + k)
+    if dtype == torch.float32:
+        u = round_f32(u)
+    announce(f"convective split k={k} {dtype} n_el={n_el}")
+    y = dgmf.apply_convective(dgmf.make_desc(k, n_el, length, lf_factor=0.5), to_dev(u, dtype))
+    ref = convective_apply(u, k, msh, lf_factor=0.5)
+    assert rel_err(y.double().cpu().numpy(), ref) < (1e-12 if dtype == torch.float64 else 1e-5)
+
+
 def test_unsupported_nq():
     d = dgmf.make_desc(3, 4, n_q=4)
     u = torch.zeros((3, 64, 64), dtype=torch.float64, device="cuda")
