@@ -253,6 +253,16 @@ struct EoT {
   }
 };
 
+// v of the lane at byte address src4 / 4 of the wavefront; every lane that
+// reads or is read is active.
+__device__ __forceinline__ float lane_get(int src4, float v) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(src4, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_get(int src4, double v) {
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(src4, __double2hiint(v)),
+                          __builtin_amdgcn_ds_bpermute(src4, __double2loint(v)));
+}
+
 // LLF flux of component values um/up (own/neighbour) with normal velocities
 // unm/unp (already signed by the outward normal), scaled by wgt.
 template <typename T>

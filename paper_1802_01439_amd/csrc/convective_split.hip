@@ -116,16 +116,6 @@ __device__ __forceinline__ decltype(auto) split_pick(const SplitTab<N, Q, T>& ct
       sizeof(T) == 4 ? split_tab_ct<N, Q, T>() : SplitTab<N, Q, T>{}; \
   const auto& t = split_pick<N, Q, T>(t##_ct, tab)
 
-// v of the lane at byte address src4 / 4 of the wavefront; every lane that
-// reads or is read is active.
-__device__ __forceinline__ float lane_get(int src4, float v) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(src4, __float_as_int(v)));
-}
-__device__ __forceinline__ double lane_get(int src4, double v) {
-  return __hiloint2double(__builtin_amdgcn_ds_bpermute(src4, __double2hiint(v)),
-                          __builtin_amdgcn_ds_bpermute(src4, __double2loint(v)));
-}
-
 // LDS layout of one element (units of T).
 //  Slots: slot a*3 + j is a column block of component j.  Forward: a = 0..n+1
 //   are the x layers -1..n, entry (b, q3), after P2 (q2, q3), at q3 + m b.

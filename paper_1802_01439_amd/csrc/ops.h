@@ -69,6 +69,9 @@ hipError_t launch_convective(const ConvPlan& P, bool f32, const void* u, void* r
 hipError_t launch_convective_split(const ConvPlan& P, bool f32, const void* u, void* r, hipStream_t s);
 hipError_t launch_convective_vjp(const ConvPlan& P, bool f32, const void* u, const void* w,
                                  void* g, hipStream_t s);
+// degrees 2..11 (FP64) and 4..11 (FP32), called by launch_convective_vjp
+hipError_t launch_convective_vjp_split(const ConvPlan& P, bool f32, const void* u, const void* w, void* g,
+                                       hipStream_t s);
 
 // Central-flux divergence: 1D mass and the 1D divergence operator on [0,1].
 struct DivPlan {

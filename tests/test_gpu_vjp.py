@@ -110,6 +110,24 @@ def test_input_alignment_fp32(k):
     assert rel_err(ga.double().cpu().numpy(), convective_vjp(u, w, k, msh)) < 1e-5
 
 
+@pytest.mark.parametrize("k,n_el", [(k, (1, 1, 1)) for k in range(2, 12)] + [(k, (2, 1, 3)) for k in range(2, 9)])
+def test_meshes_of_few_elements(k, n_el):
+    """Every degree in FP64 and FP32 where an element is its own neighbour in
+    some direction (1 per direction) or has the same neighbour on both sides
+    (2); inputs that FP32 holds exactly.  Tolerances of this file: FP64 1e-12,
+    FP32 1e-5."""
+    length = (1.0, 2.0, 0.5)
+    msh = M.Mesh(n_el, length)
+    u = round_f32(inputs.uniform((3, msh.N, (k + 1) ** 3), seed=1600 + k))
+    w = round_f32(inputs.uniform(u.shape, seed=1700 + k))
+    ref = convective_vjp(u, w, k, msh, lf_factor=0.6)
+    d = dgmf.make_desc(k, n_el, length, lf_factor=0.6)
+    for dtype, tol in ((torch.float64, 1e-12), (torch.float32, 1e-5)):
+        announce(f"vjp few elements k={k} {dtype} n_el={n_el}")
+        g = dgmf.vjp_convective(d, to_dev(u, dtype), to_dev(w, dtype))
+        assert rel_err(g.double().cpu().numpy(), ref) < tol
+
+
 def test_exact_ties_follow_half_half_convention():
     k = 2
     msh = M.cube(2)
