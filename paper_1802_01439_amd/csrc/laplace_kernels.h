@@ -37,8 +37,16 @@
 // layer steps and register pressure cost more than the neighbour loads it
 // saves): one workgroup per batch of E = floor(256/n^2) consecutive
 // elements, batches walked strip by strip, XCD by XCD; each thread first
-// issues all of its global loads (own z column and the six neighbour pencils,
-// reduced at once to end values and slopes), then the same five phases.
+// issues all of its global loads (own z column and the neighbour pencils,
+// reduced at once to end values and slopes), then the same five phases.  What
+// bounds it is the address unit: waves wait for issue 60 % of their cycles
+// (VALU busy 39 %, LDS 32 % at FP64 k = 7), since an x-neighbour pencil per
+// lane makes each load instruction touch 64 cache lines, and reading both
+// took as long as all other loads together.  x-neighbours in the same batch
+// are therefore read from LDS in the X phase; only pencils across a batch or
+// row end come from memory.  Degree-sweep meshes, us: FP64 k = 5 109 -> 98,
+// 6 118 -> 105, 7 95 -> 86, 8 101 -> 97; FP32 k = 6 69 -> 64, 7 51 -> 43,
+// 10 56 -> 53 (bit-identical); 384 or 512 threads: 0-70 % slower.
 //
 // The 1D tables are a small device table read through the scalar unit.  No
 // atomics.
@@ -330,7 +338,7 @@ struct Pencils {
 
 template <int N, typename T, typename IO>
 __device__ __forceinline__ void load_pencils(const IO& io, const MeshArgs& mesh, const BatchPos& b, int p0, int p1,
-                                             Pencils<N, T>& P) {
+                                             bool inL, bool inR, Pencils<N, T>& P) {
   constexpr int N2 = N * N, N3 = N * N * N;
   const size_t cs = (size_t)b.comp * mesh.n_el * N3;
   const int e = b.eg - b.comp * mesh.n_el;
@@ -350,8 +358,16 @@ __device__ __forceinline__ void load_pencils(const IO& io, const MeshArgs& mesh,
     P.zr[c] = io.load(zr + N2 * c, lz + N2 * c);
     P.yl[c] = io.load(yl + N * c, ly + N * c);
     P.yr[c] = io.load(yr + N * c, ly + N * c);
-    P.xl[c] = io.load(xl + c, lx + c);
-    P.xr[c] = io.load(xr + c, lx + c);
+  }
+  // x pencils of neighbours outside the batch: a wavefront reads up to 64 cache
+  // lines with each load instruction
+  if (!inL) {
+#pragma unroll
+    for (int c = 0; c < N; ++c) P.xl[c] = io.load(xl + c, lx + c);
+  }
+  if (!inR) {
+#pragma unroll
+    for (int c = 0; c < N; ++c) P.xr[c] = io.load(xr + c, lx + c);
   }
 }
 
@@ -366,17 +382,32 @@ struct BatchIn {
 };
 
 template <int N, typename T>
-__device__ __forceinline__ void reduce_pencils(const LapTab<N, T>& t, const Pencils<N, T>& P, BatchIn<N, T>& I) {
+__device__ __forceinline__ void reduce_pencils(const LapTab<N, T>& t, const Pencils<N, T>& P, bool inL, bool inR,
+                                               BatchIn<N, T>& I) {
 #pragma unroll
   for (int c = 0; c < N; ++c) I.own[c] = P.own[c];
   I.fz = nbr_face<N, T>(t, P.zl, P.zr);
   I.fy = nbr_face<N, T>(t, P.yl, P.yr);
-  I.fx = nbr_face<N, T>(t, P.xl, P.xr);
+  I.fx.vL = I.fx.gL = I.fx.vR = I.fx.gR = T(0);
+  if (!inL) {
+    T g = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) g = fmadd(t.hd1[j], P.xl[j], g);
+    I.fx.vL = P.xl[N - 1];
+    I.fx.gL = g;
+  }
+  if (!inR) {
+    T g = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) g = fmadd(t.hd0[j], P.xr[j], g);
+    I.fx.vR = P.xr[0];
+    I.fx.gR = g;
+  }
 }
 
 template <int N, typename T, typename IO>
 __device__ __forceinline__ void laplace_batch(const LapTab<N, T>& t, const BatchPos& b, const BatchIn<N, T>& I,
-                                              IO& io, T* Ue, T* Ve, int p0, int p1) {
+                                              bool inL, bool inR, IO& io, T* Ue, T* Ve, int p0, int p1) {
   using C = LapCfgB<N>;
   constexpr int N2 = C::N2, N3 = C::N3, PX = C::PX, PY = C::PY;
   T in[N], v[N], out[N];
@@ -407,12 +438,27 @@ __device__ __forceinline__ void laplace_batch(const LapTab<N, T>& t, const Batch
   // X: pencil (b,c) = (p0,p1): V += c_x Lx u, then V <- Mx V
   if (b.active) {
     const int base = PX * p0 + PY * p1;
+    NbrFace<T> fx = I.fx;
+    if (inL) {   // the neighbour's pencil is in LDS
+      T g = 0;
+#pragma unroll
+      for (int a = 0; a < N; ++a) g = fmadd(t.hd1[a], Ue[base + a - C::ES], g);
+      fx.vL = Ue[base + N - 1 - C::ES];
+      fx.gL = g;
+    }
+    if (inR) {
+      T g = 0;
+#pragma unroll
+      for (int a = 0; a < N; ++a) g = fmadd(t.hd0[a], Ue[base + a + C::ES], g);
+      fx.vR = Ue[base + C::ES];
+      fx.gR = g;
+    }
 #pragma unroll
     for (int a = 0; a < N; ++a) {
       in[a] = Ue[base + a];
       v[a] = Ve[base + a];
     }
-    l_pencil<N, T, true>(t, 0, in, I.fx, v);
+    l_pencil<N, T, true>(t, 0, in, fx, v);
     mass_pencil<N, T>(t, v, out);
 #pragma unroll
     for (int a = 0; a < N; ++a) Ve[base + a] = out[a];
@@ -458,13 +504,14 @@ laplace_batch_kernel(IO io, MeshArgs mesh, Traversal tv, const LapTab<N, T>* __r
   const int le = tid / N2, p = tid - le * N2;
   const int p0 = p % N, p1 = p / N;
   const BatchPos b = batch_pos(xcd_remap(blockIdx.x, gridDim.x), tv, mesh, E, le);
+  const bool inL = E > 1 && le > 0 && b.ex > 0, inR = E > 1 && le + 1 < b.ne && b.ex + 1 < mesh.nx;
   BatchIn<N, T> I;
   if (b.active) {
     Pencils<N, T> P;
-    load_pencils<N, T>(io, mesh, b, p0, p1, P);
-    reduce_pencils<N, T>(t, P, I);
+    load_pencils<N, T>(io, mesh, b, p0, p1, inL, inR, P);
+    reduce_pencils<N, T>(t, P, inL, inR, I);
   }
-  laplace_batch<N, T>(t, b, I, io, U + le * ES, V + le * ES, p0, p1);
+  laplace_batch<N, T>(t, b, I, inL, inR, io, U + le * ES, V + le * ES, p0, p1);
   io.template finish<C::THREADS, sizeof(UV)>(UV);
 }
 
