@@ -32,24 +32,24 @@ hipError_t launch_laplace(const LaplacePlan& P, bool f32, const void* src, void*
 // host_out, also writes the table there (for an upload by the caller).
 size_t lap_table_fill(const LaplacePlan& P, bool f32, void* host_out);
 
-// Multigrid smoother steps fused into the Laplace apply (T = double, float):
-// d <- c1 d + c2 D^-1 (b - A x), xout = x + d (xout must not be x: x is read
-// for neighbour DoFs); res = b - A x.  dinv: one element's n^3 values.
+// One step of the multigrid smoother (zero-start Chebyshev) fused into the
+// Laplace apply (T = double, float):
+//   x_{j+1} = x_j + c1 (x_j - x_{j-1}) + c2 D^-1 (b - A x_j),  x_1 = s D^-1 b
+// x: x_j, NULL for j = 1 (formed from b); prev: x_{j-1}, NULL for j = 1, 2;
+// out: must not be x, may be prev; add: out += x_{j+1} instead (j >= 3).
+// dinv: one element's n^3 values.
 template <typename T>
-hipError_t mg_apply_cheb(const LaplacePlan& P, const T* x, const T* b, const T* dinv, T c1, T c2, T* d, T* xout,
-                         hipStream_t s);
+struct MgChebStep {
+  const T *x, *b, *dinv, *prev;
+  T* out;
+  T s, c1, c2;
+  bool add;
+};
+template <typename T>
+hipError_t mg_apply_cheb(const LaplacePlan& P, const MgChebStep<T>& st, hipStream_t s);
+// res = b - A x
 template <typename T>
 hipError_t mg_apply_residual(const LaplacePlan& P, const T* x, const T* b, T* res, hipStream_t s);
-// the Chebyshev step of mg_apply_cheb with its new iterate added to y
-// (y += x + d') instead of stored
-template <typename T>
-hipError_t mg_apply_cheb_add(const LaplacePlan& P, const T* x, const T* b, const T* dinv, T c1, T c2, const T* d, T* y,
-                             hipStream_t s);
-// res = b - A x and the first step of a zero-start Chebyshev smoother on it,
-// d = e = scale * dinv[node] * res
-template <typename T>
-hipError_t mg_apply_residual_cheb_first(const LaplacePlan& P, const T* x, const T* b, const T* dinv, T scale, T* res,
-                                        T* d, T* e, hipStream_t s);
 
 // Convective form and its VJP: 1D tables on [0,1] and the cell/face scalings.
 struct ConvPlan {
@@ -99,11 +99,6 @@ hipError_t launch_transfer(const TransferPlan& P, bool prolong, bool f32, const 
                            hipStream_t s);
 // dst += the prolongation of src (a V-cycle's coarse-grid correction)
 hipError_t launch_prolongate_add(const TransferPlan& P, bool f32, const void* src, void* dst, hipStream_t s);
-// rc = the restriction of rf (one component) and the first step of a
-// zero-start Chebyshev smoother on it: d = x = scale * dinv[node] * rc, with
-// scale rounded to the transfer's precision
-hipError_t launch_restrict_cheb_first(const TransferPlan& P, bool f32, const void* rf, void* rc, const void* dinv,
-                                      double scale, void* d, void* x, hipStream_t s);
 
 // pressure gradient: the divergence's 1D tables, G = -B^T
 hipError_t launch_gradient(const DivPlan& P, bool f32, const void* p, void* y, hipStream_t s);

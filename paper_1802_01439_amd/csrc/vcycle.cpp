@@ -11,9 +11,10 @@
 //   x += Cheb_l(b - A_l x)                          post-smoothing
 // and on the coarsest level x = Cheb(b) of the coarse degree.  Cheb is the
 // zero-start Chebyshev iteration of D^-1 A on [lambda_max/range, lambda_max]
-// in its three-term form; its scalars are formed on the host, and its steps
-// after the first, like the residuals b - A_l x, run in the epilogue of the
-// Laplace apply.
+// in its three-term form; its scalars are formed on the host, and its steps,
+// like the residuals b - A_l x, run in the Laplace apply.  The fine level is
+// bound by HBM: with the step direction kept as a vector of its own and the
+// first iterate written out, a cycle moved 52 fine-level vectors, now 33.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -73,7 +74,7 @@ struct MgLevel {
   LaplacePlan plan;
   long long n = 0;
   double lmax = 0;
-  T *dinv = nullptr, *b = nullptr, *x = nullptr, *t = nullptr, *d = nullptr, *res = nullptr, *e = nullptr;
+  T *dinv = nullptr, *b = nullptr, *x = nullptr, *t = nullptr, *res = nullptr, *e = nullptr;
 };
 
 // the cycle's vectors and arithmetic in T (double or float)
@@ -106,54 +107,34 @@ struct MgRun {
     return e;
   }
 
-  // 1 / theta of level l's Chebyshev interval [lmax / range, lmax]
-  double cheb_scale(const MgLevel<T>& L) const { return 1.0 / (0.5 * (L.lmax + L.lmax / range)); }
-
-  // x = Cheb(b) on level l (deg steps, deg - 1 operator applications);
-  // first_done: the first step (d = x = D^-1 b / theta) was taken by the
-  // kernel that produced b.  add_to: the last step, where it is a fused
-  // step, adds its iterate to add_to instead of storing it (then *added)
-  hipError_t cheb(MgLevel<T>& L, const T* b, T* x, int deg, bool first_done = false, T* add_to = nullptr,
-                  bool* added = nullptr) {
-    if (added) *added = false;
+  // x = Cheb(b) on level l (deg steps, deg - 1 operator applications, each
+  // with its step fused), with L.t as the second vector of the iteration.
+  // add_to: the iterate is added to add_to instead (x is then work space)
+  hipError_t cheb(MgLevel<T>& L, const T* b, T* x, int deg, T* add_to = nullptr) {
     const double lmin = L.lmax / range;
     const double theta = 0.5 * (L.lmax + lmin), delta = 0.5 * (L.lmax - lmin);
+    const T scale = (T)(1.0 / theta);
+    const int m = deg - 1;
     hipError_t e;
-    if (!first_done && (e = mg_cheb_first(b, L.dinv, n3, (T)cheb_scale(L), L.d, x, L.n, s)) != hipSuccess) return e;
+    if (m == 0 && (e = mg_cheb_first(b, L.dinv, n3, scale, x, L.n, s)) != hipSuccess) return e;
+    // application j of m writes x_{j+1}: to x and L.t in turn, the last to x
+    T* buf[2] = {x, L.t};
+    const T *cur = nullptr, *prev = nullptr;
     double rho_prev = delta / theta;
-    int step = 1;
-    if ((deg - 1) % 2 == 1) {
-      // an odd number of steps: the first one apart (apply, then the update
-      // in place), so that the fused steps, which alternate between x and
-      // L.t, end in x
-      if ((e = launch_laplace(L.plan, F32, x, L.t, s)) != hipSuccess) return e;
-      ++applies;
+    for (int j = 1; j <= m; ++j) {
       const double rho = 1.0 / (2.0 * theta / delta - rho_prev);
-      if ((e = mg_cheb_next(b, L.t, L.dinv, n3, (T)(rho * rho_prev), (T)(2.0 * rho / delta), L.d, x, L.n, s)) !=
-          hipSuccess)
-        return e;
-      rho_prev = rho;
-      step = 2;
-    }
-    T *cur = x, *nxt = L.t;
-    for (; step < deg; ++step) {
-      const double rho = 1.0 / (2.0 * theta / delta - rho_prev);
-      if (add_to && step == deg - 1) {
-        if ((e = mg_apply_cheb_add<T>(L.plan, cur, b, L.dinv, (T)(rho * rho_prev), (T)(2.0 * rho / delta), L.d, add_to,
-                                      s)) != hipSuccess)
-          return e;
-        ++applies;
-        if (added) *added = true;
-        return hipSuccess;
-      }
-      if ((e = mg_apply_cheb<T>(L.plan, cur, b, L.dinv, (T)(rho * rho_prev), (T)(2.0 * rho / delta), L.d, nxt, s)) !=
-          hipSuccess)
-        return e;
+      const bool add = add_to && j == m && j >= 3;
+      T* out = buf[(m - j) & 1];
+      const MgChebStep<T> st{cur,   b, L.dinv, prev, add ? add_to : out, scale, (T)(rho * rho_prev),
+                             (T)(2.0 * rho / delta), add};
+      if ((e = mg_apply_cheb<T>(L.plan, st, s)) != hipSuccess) return e;
       ++applies;
-      std::swap(cur, nxt);
+      if (add) return hipSuccess;
+      prev = cur;
+      cur = out;
       rho_prev = rho;
     }
-    return hipSuccess;
+    return add_to ? mg_add(add_to, x, L.n, s) : hipSuccess;
   }
 
   TransferPlan transfer_plan(int coarse) const {
@@ -168,29 +149,22 @@ struct MgRun {
     return TP;
   }
 
-  // lv[l].x = cycle(l, lv[l].b); first_done: see cheb
-  hipError_t cycle(int l, bool first_done = false) {
+  // lv[l].x = cycle(l, lv[l].b)
+  hipError_t cycle(int l) {
     MgLevel<T>& L = lv[l];
     hipError_t e;
     const bool last = l + 1 == (int)lv.size();
-    if ((e = cheb(L, L.b, L.x, last ? coarse_degree : degree, first_done)) != hipSuccess) return e;
+    if ((e = cheb(L, L.b, L.x, last ? coarse_degree : degree)) != hipSuccess) return e;
     if (last) return hipSuccess;
     if ((e = mg_apply_residual<T>(L.plan, L.x, L.b, L.res, s)) != hipSuccess) return e;
     ++applies;
     const TransferPlan TP = transfer_plan(l + 1);
-    MgLevel<T>& Lc = lv[l + 1];
-    if ((e = launch_restrict_cheb_first(TP, F32, L.res, Lc.b, Lc.dinv, (double)(T)cheb_scale(Lc), Lc.d, Lc.x, s)) !=
-        hipSuccess)
-      return e;
-    if ((e = cycle(l + 1, true)) != hipSuccess) return e;
+    if ((e = launch_transfer(TP, false, F32, L.res, lv[l + 1].b, s)) != hipSuccess) return e;
+    if ((e = cycle(l + 1)) != hipSuccess) return e;
     if ((e = launch_prolongate_add(TP, F32, lv[l + 1].x, L.x, s)) != hipSuccess) return e;
-    if ((e = mg_apply_residual_cheb_first<T>(L.plan, L.x, L.b, L.dinv, (T)cheb_scale(L), L.res, L.d, L.e, s)) !=
-        hipSuccess)
-      return e;
+    if ((e = mg_apply_residual<T>(L.plan, L.x, L.b, L.res, s)) != hipSuccess) return e;
     ++applies;
-    bool added = false;
-    if ((e = cheb(L, L.res, L.e, degree, true, L.x, &added)) != hipSuccess) return e;
-    return added ? hipSuccess : mg_add(L.x, L.e, L.n, s);
+    return cheb(L, L.res, L.e, degree, L.x);
   }
 };
 
@@ -257,9 +231,9 @@ int mg_setup(MgRun<T>& M, const dg_op_desc* desc, int levels, int degree, double
     if ((e = hipMemcpyAsync(L.dinv, dinv.data(), M.n3 * sizeof(T), hipMemcpyHostToDevice, M.s)) != hipSuccess)
       return hip_fail(e, "V-cycle tables");
     if ((e = hipStreamSynchronize(M.s)) != hipSuccess) return hip_fail(e, "V-cycle tables");
-    T** bufs[5] = {&L.t, &L.d, &L.res, &L.e, &L.b};
+    T** bufs[4] = {&L.t, &L.res, &L.e, &L.b};
     const bool top = l > 0 || own_top;
-    for (int i = 0; i < (top ? 5 : 4); ++i)
+    for (int i = 0; i < (top ? 4 : 3); ++i)
       if ((e = M.alloc(bufs[i], L.n)) != hipSuccess) return hip_fail(e, "V-cycle work vectors");
     if (top && (e = M.alloc(&L.x, L.n)) != hipSuccess) return hip_fail(e, "V-cycle work vectors");
   }

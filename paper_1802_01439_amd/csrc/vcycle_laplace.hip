@@ -1,15 +1,20 @@
 // Multigrid smoother work fused into the epilogue of the Laplace apply
-// (Sec. 3.3, the V-cycle's Chebyshev smoother), FP64 and FP32:
-//   Chebyshev step  d <- c1 d + c2 D^-1 (b - A x),  x' = x + d
-//   residual        res = b - A x
-//   residual and the first step of a zero-start Chebyshev smoother on it
-//                   res = b - A x,  d = e = s D^-1 res
-//   last Chebyshev step of the post-smoothing, added to the level's iterate
-//                   y += x + (c1 d + c2 D^-1 (b - A x))
-// The operand x is read for neighbour DoFs by other workgroups, so the new
-// iterate goes to a second buffer x'; d is read and written only by the
-// thread that owns each DoF, in place.  D^-1 is one element's diagonal
-// inverse, indexed by the local node.
+// (Sec. 3.3, the V-cycle's Chebyshev smoother from a zero start), FP64 and
+// FP32.  A step needs no vector of its own for the step direction, since
+// that is the difference of the last two iterates:
+//   x_{j+1} = x_j + c1 (x_j - x_{j-1}) + c2 D^-1 (b - A x_j),
+// and the first iterate x_1 = s D^-1 b is formed from b wherever it is read:
+//   first   x_2 from b alone              (reads b, writes x_2)
+//   second  x_3, x_1 formed from b        (reads x_2, b, writes x_3)
+//   later   x_{j+1} over x_{j-1}          (reads x_j, x_{j-1}, b, writes)
+//   added   the last step of the post-smoothing, y += x_{j+1}
+//   residual  res = b - A x
+// The operand x_j is read for neighbour DoFs by other workgroups, x_{j-1} only
+// by the thread that owns each DoF, which overwrites it.  D^-1 is one
+// element's diagonal inverse, indexed by the local node.
+// Bound: HBM.  A smoothing of degree 5 moves 13 vectors (23 with the step
+// direction stored, x_1 written by a kernel of its own), the post-smoothing
+// with its residual 17 (26 before).
 #include "laplace_kernels.h"
 #include "ops.h"
 
@@ -17,20 +22,29 @@ namespace dgmf {
 
 namespace {
 
-template <typename T>
+enum { kFirst, kSecond, kLater };
+
+template <typename T, int KIND, bool ADD>
 struct MgChebIO {
-  const T* __restrict__ x;
-  const T* __restrict__ b;
+  const T* x;   // operand (unused by the first step)
+  const T* b;
   const T* __restrict__ dinv;
-  T* __restrict__ d;
-  T* __restrict__ xout;
-  T c1, c2;
+  const T* prev;   // x_{j-1} (later steps); out may be the same vector
+  T* out;
+  T s, c1, c2;
   __device__ __forceinline__ void begin() {}
-  __device__ __forceinline__ T load(size_t i, int) const { return x[i]; }
-  __device__ __forceinline__ void store(size_t i, int loc, T in, T out) {
-    const T v = c1 * d[i] + c2 * dinv[loc] * (b[i] - out);
-    d[i] = v;
-    xout[i] = in + v;
+  __device__ __forceinline__ T load(size_t i, int loc) const {
+    if constexpr (KIND == kFirst) return s * dinv[loc] * b[i];
+    else return x[i];
+  }
+  __device__ __forceinline__ void store(size_t i, int loc, T in, T ax) {
+    const T bi = b[i], di = dinv[loc];
+    T step = in;   // x_j - x_{j-1}
+    if constexpr (KIND == kSecond) step -= s * di * bi;
+    if constexpr (KIND == kLater) step -= prev[i];
+    const T xn = in + (c1 * step + c2 * di * (bi - ax));
+    if constexpr (ADD) out[i] += xn;
+    else out[i] = xn;
   }
   template <int THREADS, size_t BYTES>
   __device__ __forceinline__ void finish(void*) {}
@@ -44,47 +58,6 @@ struct MgResIO {
   __device__ __forceinline__ void begin() {}
   __device__ __forceinline__ T load(size_t i, int) const { return x[i]; }
   __device__ __forceinline__ void store(size_t i, int, T, T out) { res[i] = b[i] - out; }
-  template <int THREADS, size_t BYTES>
-  __device__ __forceinline__ void finish(void*) {}
-};
-
-template <typename T>
-struct MgChebAddIO {
-  const T* __restrict__ x;
-  const T* __restrict__ b;
-  const T* __restrict__ dinv;
-  const T* __restrict__ d;
-  T* __restrict__ y;
-  T c1, c2;
-  __device__ __forceinline__ void begin() {}
-  __device__ __forceinline__ T load(size_t i, int) const { return x[i]; }
-  __device__ __forceinline__ void store(size_t i, int loc, T in, T out) {
-    const T v = c1 * d[i] + c2 * dinv[loc] * (b[i] - out);
-    const T xn = in + v;
-    y[i] = y[i] + xn;
-  }
-  template <int THREADS, size_t BYTES>
-  __device__ __forceinline__ void finish(void*) {}
-};
-
-template <typename T>
-struct MgResChebIO {
-  const T* __restrict__ x;
-  const T* __restrict__ b;
-  const T* __restrict__ dinv;
-  T* __restrict__ res;
-  T* __restrict__ d;
-  T* __restrict__ e;
-  T s;
-  __device__ __forceinline__ void begin() {}
-  __device__ __forceinline__ T load(size_t i, int) const { return x[i]; }
-  __device__ __forceinline__ void store(size_t i, int loc, T, T out) {
-    const T r = b[i] - out;
-    res[i] = r;
-    const T v = s * dinv[loc] * r;
-    d[i] = v;
-    e[i] = v;
-  }
   template <int THREADS, size_t BYTES>
   __device__ __forceinline__ void finish(void*) {}
 };
@@ -110,10 +83,18 @@ hipError_t dispatch(const LaplacePlan& P, const IO& io, hipStream_t s) {
 }  // namespace
 
 template <typename T>
-hipError_t mg_apply_cheb(const LaplacePlan& P, const T* x, const T* b, const T* dinv, T c1, T c2, T* d, T* xout,
-                         hipStream_t s) {
-  MgChebIO<T> io{x, b, dinv, d, xout, c1, c2};
-  return dispatch<T>(P, io, s);
+hipError_t mg_apply_cheb(const LaplacePlan& P, const MgChebStep<T>& st, hipStream_t s) {
+  if (!st.x) {
+    if (st.add) return hipErrorInvalidValue;
+    return dispatch<T>(P, MgChebIO<T, kFirst, false>{nullptr, st.b, st.dinv, nullptr, st.out, st.s, st.c1, st.c2}, s);
+  }
+  if (!st.prev) {
+    if (st.add) return hipErrorInvalidValue;
+    return dispatch<T>(P, MgChebIO<T, kSecond, false>{st.x, st.b, st.dinv, nullptr, st.out, st.s, st.c1, st.c2}, s);
+  }
+  if (st.add)
+    return dispatch<T>(P, MgChebIO<T, kLater, true>{st.x, st.b, st.dinv, st.prev, st.out, st.s, st.c1, st.c2}, s);
+  return dispatch<T>(P, MgChebIO<T, kLater, false>{st.x, st.b, st.dinv, st.prev, st.out, st.s, st.c1, st.c2}, s);
 }
 
 template <typename T>
@@ -122,34 +103,9 @@ hipError_t mg_apply_residual(const LaplacePlan& P, const T* x, const T* b, T* re
   return dispatch<T>(P, io, s);
 }
 
-template <typename T>
-hipError_t mg_apply_cheb_add(const LaplacePlan& P, const T* x, const T* b, const T* dinv, T c1, T c2, const T* d, T* y,
-                             hipStream_t s) {
-  MgChebAddIO<T> io{x, b, dinv, d, y, c1, c2};
-  return dispatch<T>(P, io, s);
-}
-
-template <typename T>
-hipError_t mg_apply_residual_cheb_first(const LaplacePlan& P, const T* x, const T* b, const T* dinv, T scale, T* res,
-                                        T* d, T* e, hipStream_t s) {
-  MgResChebIO<T> io{x, b, dinv, res, d, e, scale};
-  return dispatch<T>(P, io, s);
-}
-
-template hipError_t mg_apply_cheb<double>(const LaplacePlan&, const double*, const double*, const double*, double,
-                                          double, double*, double*, hipStream_t);
-template hipError_t mg_apply_cheb<float>(const LaplacePlan&, const float*, const float*, const float*, float, float,
-                                         float*, float*, hipStream_t);
+template hipError_t mg_apply_cheb<double>(const LaplacePlan&, const MgChebStep<double>&, hipStream_t);
+template hipError_t mg_apply_cheb<float>(const LaplacePlan&, const MgChebStep<float>&, hipStream_t);
 template hipError_t mg_apply_residual<double>(const LaplacePlan&, const double*, const double*, double*, hipStream_t);
 template hipError_t mg_apply_residual<float>(const LaplacePlan&, const float*, const float*, float*, hipStream_t);
-template hipError_t mg_apply_cheb_add<double>(const LaplacePlan&, const double*, const double*, const double*, double,
-                                              double, const double*, double*, hipStream_t);
-template hipError_t mg_apply_cheb_add<float>(const LaplacePlan&, const float*, const float*, const float*, float, float,
-                                             const float*, float*, hipStream_t);
-template hipError_t mg_apply_residual_cheb_first<double>(const LaplacePlan&, const double*, const double*,
-                                                         const double*, double, double*, double*, double*,
-                                                         hipStream_t);
-template hipError_t mg_apply_residual_cheb_first<float>(const LaplacePlan&, const float*, const float*, const float*,
-                                                        float, float*, float*, float*, hipStream_t);
 
 }  // namespace dgmf
