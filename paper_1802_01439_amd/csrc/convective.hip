@@ -519,9 +519,9 @@ static hipError_t launch_conv_nq(const ConvPlan& P, const void* u, void* r, hipS
   sc.lf = (T)P.lf;
   const ConvTab<N, Q, T>* dt = nullptr;   // FP32 kernels use the compile-time tables
   if (sizeof(T) == 8) {
-    const ConvTab<N, Q, T> t = make_conv_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data());
     hipError_t err;
-    dt = device_table_of("convective", t, &err);
+    dt = plan_table<ConvTab<N, Q, T>>(
+        P.tab.p[0], "convective", [&] { return make_conv_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data()); }, &err);
     if (!dt) return err;
   }
   const int grid = (P.mesh.n_el + Sh::E - 1) / Sh::E;

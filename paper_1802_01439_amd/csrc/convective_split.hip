@@ -528,9 +528,9 @@ static hipError_t launch_split_nq(const ConvPlan& P, const void* u, void* r, hip
   sc.lf = (T)P.lf;
   const SplitTab<N, Q, T>* dt = nullptr;   // FP32 kernels use the compile-time tables
   if (sizeof(T) == 8) {
-    const SplitTab<N, Q, T> t = make_split_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data());
     hipError_t err;
-    dt = device_table_of("convective_split", t, &err);
+    dt = plan_table<SplitTab<N, Q, T>>(
+        P.tab.p[0], "convective_split", [&] { return make_split_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data()); }, &err);
     if (!dt) return err;
   }
   int grid = P.mesh.n_el;

@@ -556,9 +556,9 @@ static hipError_t launch_vjp_nq(const ConvPlan& P, const void* u, const void* w,
   sc.lf = (T)P.lf;
   const ConvTab<N, Q, T>* dt = nullptr;   // FP32 kernels use the compile-time tables
   if (sizeof(T) == 8) {
-    const ConvTab<N, Q, T> t = make_conv_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data());
     hipError_t err;
-    dt = device_table_of("convective", t, &err);
+    dt = plan_table<ConvTab<N, Q, T>>(
+        P.tab.p[1], "convective", [&] { return make_conv_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data()); }, &err);
     if (!dt) return err;
   }
   // every pencil of n contiguous values starts at a multiple of n values from

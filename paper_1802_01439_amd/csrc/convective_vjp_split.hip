@@ -510,9 +510,9 @@ static hipError_t launch_vjp_split_nq(const ConvPlan& P, const void* u, const vo
   sc.lf = (T)P.lf;
   const VjpTab<N, Q, T>* dt = nullptr;   // FP32 kernels use the compile-time tables
   if (sizeof(T) == 8) {
-    const VjpTab<N, Q, T> t = make_vjp_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data());
     hipError_t err;
-    dt = device_table_of("vjp_split", t, &err);
+    dt = plan_table<VjpTab<N, Q, T>>(
+        P.tab.p[1], "vjp_split", [&] { return make_vjp_tab<N, Q, T>(P.S.data(), P.G.data(), P.w.data()); }, &err);
     if (!dt) return err;
   }
   // FP64: z first, so that a wavefront's loads and stores are contiguous.

@@ -875,12 +875,15 @@ long lap_grid(const LaplacePlan& P) {
   }
 }
 
-// Launch y = A x through io.  tab: device table from lap_device_tab (or
-// nullptr to look it up here).
+// Launch y = A x through io.  tab: device table from lap_device_tab, or
+// nullptr to take the plan's (looked up at its first launch).
 template <int N, typename T, typename IO>
 hipError_t launch_laplace_io(const LaplacePlan& P, const IO& io, const LapTab<N, T>* tab, hipStream_t stream) {
-  hipError_t err;
-  if (!tab && !(tab = lap_device_tab<N, T>(P, &err))) return err;
+  if (!tab) {
+    hipError_t err;
+    tab = plan_table<LapTab<N, T>>(P.tab.p[sizeof(T) == 4], "laplace", [&] { return make_lap_tab<N, T>(P); }, &err);
+    if (!tab) return err;
+  }
   if constexpr (!lap_march<N, T>()) {
     using CB = LapCfgB<N>;
     Traversal tv;

@@ -3,14 +3,33 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <atomic>
 #include <vector>
 
 #include "common.h"
 
 namespace dgmf {
 
+// Device tables of one plan, each looked up at the first launch that needs it
+// (device_table never frees one): building and hashing the table is most of a
+// launch's host time at high degrees, and a V-cycle launches one plan some ten
+// times.  A copy of a plan starts without them: it may be changed before it is
+// launched.
+struct TabSlots {
+  std::atomic<const void*> p[2] = {nullptr, nullptr};
+  TabSlots() = default;
+  TabSlots(const TabSlots&) {}
+  TabSlots& operator=(const TabSlots&) {
+    p[0] = nullptr;
+    p[1] = nullptr;
+    return *this;
+  }
+};
+
 // Everything a Laplace launch needs, in double; kernels cast to their type.
 struct LaplacePlan {
+  mutable TabSlots tab;   // FP64, FP32
   int k = 0;
   int n_comp = 1;
   MeshArgs mesh{};
@@ -53,6 +72,7 @@ hipError_t mg_apply_residual(const LaplacePlan& P, const T* x, const T* b, T* re
 
 // Convective form and its VJP: 1D tables on [0,1] and the cell/face scalings.
 struct ConvPlan {
+  mutable TabSlots tab;   // FP64: apply, VJP
   int k = 0;
   int m = 0;                 // Gauss points per direction (floor(3k/2)+1)
   MeshArgs mesh{};
@@ -106,6 +126,7 @@ hipError_t launch_gradient(const DivPlan& P, bool f32, const void* p, void* y, h
 // Projection-step operator (mass + divergence and continuity penalties):
 // 1D tables on [0,1] with k+1 Gauss points and the cell scalings.
 struct ProjPlan {
+  mutable TabSlots tab;   // FP64, FP32
   int k = 0;
   MeshArgs mesh{};
   std::vector<double> S, Dg, M1, w;   // n x n, n x n, n x n, n

@@ -338,9 +338,7 @@ bool make_eo(const double* A, int sig, EOMat<N, T>& m) {
 }
 
 template <int N, typename T>
-hipError_t launch_n(const ProjPlan& P, const void* u, void* yv, const void* td, const void* tc, hipStream_t s,
-                    void* dot) {
-  ProjTab<N, T> t{};
+bool make_proj_tab(const ProjPlan& P, ProjTab<N, T>& t) {
   double St[N * N], Dt[N * N];
   for (int i = 0; i < N; ++i) {
     for (int a = 0; a < N; ++a) {
@@ -352,15 +350,27 @@ hipError_t launch_n(const ProjPlan& P, const void* u, void* yv, const void* td, 
   }
   if (!make_eo<N, T>(P.S.data(), 1, t.S) || !make_eo<N, T>(St, 1, t.St) || !make_eo<N, T>(P.Dg.data(), -1, t.Dg) ||
       !make_eo<N, T>(Dt, -1, t.Dt))
-    return hipErrorInvalidValue;
+    return false;
   t.vol = (T)P.vol;
   for (int d = 0; d < 3; ++d) {
     t.ih[d] = (T)P.ih[d];
     t.area[d] = (T)P.area[d];
   }
-  hipError_t err;
-  const ProjTab<N, T>* dt = device_table_of("projection", t, &err);
-  if (!dt) return err;
+  return true;
+}
+
+template <int N, typename T>
+hipError_t launch_n(const ProjPlan& P, const void* u, void* yv, const void* td, const void* tc, hipStream_t s,
+                    void* dot) {
+  std::atomic<const void*>& slot = P.tab.p[sizeof(T) == 4];
+  const ProjTab<N, T>* dt = static_cast<const ProjTab<N, T>*>(slot.load(std::memory_order_acquire));
+  if (!dt) {
+    ProjTab<N, T> t{};
+    if (!make_proj_tab<N, T>(P, t)) return hipErrorInvalidValue;
+    hipError_t err;
+    if (!(dt = device_table_of("projection", t, &err))) return err;
+    slot.store(dt, std::memory_order_release);
+  }
   using C = ProjCfg<N>;
   const long long grid = ((long long)P.mesh.n_el + C::E - 1) / C::E;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;

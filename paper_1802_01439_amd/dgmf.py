@@ -155,9 +155,18 @@ def make_desc(degree, n_el, length=None, n_q=0, penalty_factor=1.0, scale=1.0, n
     return d
 
 
+_mod = None
+_raw_stream = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _mod, _raw_stream
+    if _mod is None:
+        import torch
+        # the current stream's handle without a Stream object, where torch has it
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _mod = torch
+    return _mod
 
 
 def _dtype_code(t):
@@ -194,13 +203,36 @@ def _placed(first, *others):
             raise ValueError("every tensor argument must be contiguous")
 
 
-def _stream(t):
+def _plain(first, shape, *others):
+    """Whether first is a contiguous GPU tensor of `shape`, and each (tensor,
+    shape) in others None or one of that shape on its device and of its dtype:
+    all that _check_tensor and _placed ask, in one pass.  Where this is False
+    the callers go through those two, which say what is wrong."""
+    if first.shape != shape or not first.is_cuda or not first.is_contiguous():
+        return False
+    dtype, dev = first.dtype, first.get_device()
+    for t, sh in others:
+        if t is not None and (t.shape != sh or t.dtype != dtype or not t.is_cuda or t.get_device() != dev
+                              or not t.is_contiguous()):
+            return False
+    return True
+
+
+def _handle(t):
+    """The current stream of t's device as an integer handle."""
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _stream(t):
+    return ctypes.c_void_p(_handle(t))
 
 
 def _nel(desc):
-    return desc.n_el[0] * desc.n_el[1] * desc.n_el[2]
+    nx, ny, nz = desc.n_el
+    return nx * ny * nz
 
 
 def apply_laplace(desc, u, out=None):
@@ -208,13 +240,15 @@ def apply_laplace(desc, u, out=None):
     torch = _torch()
     n3 = (desc.degree + 1) ** 3
     shape = (_nel(desc), n3) if desc.n_comp == 1 else (3, _nel(desc), n3)
-    _check_tensor(u, "u", shape)
-    if out is None:
+    if not _plain(u, shape, (out, shape)):
+        _check_tensor(u, "u", shape)
+        if out is None:
+            out = torch.empty_like(u)
+        _check_tensor(out, "out", shape, like=u)
+        _placed(u, out)
+    elif out is None:
         out = torch.empty_like(u)
-    _check_tensor(out, "out", shape, like=u)
-    _placed(u, out)
-    _check(lib().dg_apply_laplace(ctypes.byref(desc), _dtype_code(u), ctypes.c_void_p(u.data_ptr()),
-                                  ctypes.c_void_p(out.data_ptr()), _stream(u)))
+    _check(lib().dg_apply_laplace(desc, _dtype_code(u), u.data_ptr(), out.data_ptr(), _handle(u)))
     return out
 
 
@@ -222,13 +256,15 @@ def apply_convective(desc, u, out=None):
     """Convective LLF apply; u, out: [3, N_el, n^3]."""
     torch = _torch()
     shape = (3, _nel(desc), (desc.degree + 1) ** 3)
-    _check_tensor(u, "u", shape)
-    if out is None:
+    if not _plain(u, shape, (out, shape)):
+        _check_tensor(u, "u", shape)
+        if out is None:
+            out = torch.empty_like(u)
+        _check_tensor(out, "out", shape, like=u)
+        _placed(u, out)
+    elif out is None:
         out = torch.empty_like(u)
-    _check_tensor(out, "out", shape, like=u)
-    _placed(u, out)
-    _check(lib().dg_apply_convective(ctypes.byref(desc), _dtype_code(u), ctypes.c_void_p(u.data_ptr()),
-                                     ctypes.c_void_p(out.data_ptr()), _stream(u)))
+    _check(lib().dg_apply_convective(desc, _dtype_code(u), u.data_ptr(), out.data_ptr(), _handle(u)))
     return out
 
 
@@ -241,42 +277,48 @@ def vjp_convective(desc, u, w, out=None):
     """J(u)^T w for the convective apply; all [3, N_el, n^3]."""
     torch = _torch()
     shape = (3, _nel(desc), (desc.degree + 1) ** 3)
-    _check_tensor(u, "u", shape)
-    _check_tensor(w, "w", shape, like=u)
-    if out is None:
+    if w is None or not _plain(u, shape, (w, shape), (out, shape)):
+        _check_tensor(u, "u", shape)
+        _check_tensor(w, "w", shape, like=u)
+        if out is None:
+            out = torch.empty_like(u)
+        _check_tensor(out, "out", shape, like=u)
+        _placed(u, w, out)
+    elif out is None:
         out = torch.empty_like(u)
-    _check_tensor(out, "out", shape, like=u)
-    _placed(u, w, out)
-    _check(lib().dg_vjp_convective(ctypes.byref(desc), _dtype_code(u), ctypes.c_void_p(u.data_ptr()),
-                                   ctypes.c_void_p(w.data_ptr()), ctypes.c_void_p(out.data_ptr()), _stream(u)))
+    _check(lib().dg_vjp_convective(desc, _dtype_code(u), u.data_ptr(), w.data_ptr(), out.data_ptr(), _handle(u)))
     return out
 
 
 def apply_divergence(desc, u, out=None):
     """Central-flux divergence d_h(phi_i, u); u: [3, N_el, n^3] -> [N_el, n^3]."""
     torch = _torch()
-    n3 = (desc.degree + 1) ** 3
-    _check_tensor(u, "u", (3, _nel(desc), n3))
+    nel, n3 = _nel(desc), (desc.degree + 1) ** 3
+    ok = _plain(u, (3, nel, n3), (out, (nel, n3)))
+    if not ok:
+        _check_tensor(u, "u", (3, nel, n3))
     if out is None:
-        out = torch.empty((_nel(desc), n3), dtype=u.dtype, device=u.device)
-    _check_tensor(out, "out", (_nel(desc), n3), like=u)
-    _placed(u, out)
-    _check(lib().dg_apply_divergence(ctypes.byref(desc), _dtype_code(u), ctypes.c_void_p(u.data_ptr()),
-                                     ctypes.c_void_p(out.data_ptr()), _stream(u)))
+        out = torch.empty((nel, n3), dtype=u.dtype, device=u.device)
+    if not ok:
+        _check_tensor(out, "out", (nel, n3), like=u)
+        _placed(u, out)
+    _check(lib().dg_apply_divergence(desc, _dtype_code(u), u.data_ptr(), out.data_ptr(), _handle(u)))
     return out
 
 
 def apply_gradient(desc, p, out=None):
     """Central-flux pressure gradient g_h(phi_i e_j, p); p: [N_el, n^3] -> [3, N_el, n^3]."""
     torch = _torch()
-    n3 = (desc.degree + 1) ** 3
-    _check_tensor(p, "p", (_nel(desc), n3))
+    nel, n3 = _nel(desc), (desc.degree + 1) ** 3
+    ok = _plain(p, (nel, n3), (out, (3, nel, n3)))
+    if not ok:
+        _check_tensor(p, "p", (nel, n3))
     if out is None:
-        out = torch.empty((3, _nel(desc), n3), dtype=p.dtype, device=p.device)
-    _check_tensor(out, "out", (3, _nel(desc), n3), like=p)
-    _placed(p, out)
-    _check(lib().dg_apply_gradient(ctypes.byref(desc), _dtype_code(p), ctypes.c_void_p(p.data_ptr()),
-                                   ctypes.c_void_p(out.data_ptr()), _stream(p)))
+        out = torch.empty((3, nel, n3), dtype=p.dtype, device=p.device)
+    if not ok:
+        _check_tensor(out, "out", (3, nel, n3), like=p)
+        _placed(p, out)
+    _check(lib().dg_apply_gradient(desc, _dtype_code(p), p.data_ptr(), out.data_ptr(), _handle(p)))
     return out
 
 
@@ -376,30 +418,36 @@ def apply_helmholtz(desc, u, mass_factor, out=None):
     torch = _torch()
     n3 = (desc.degree + 1) ** 3
     shape = (_nel(desc), n3) if desc.n_comp == 1 else (3, _nel(desc), n3)
-    _check_tensor(u, "u", shape)
-    if out is None:
+    if not _plain(u, shape, (out, shape)):
+        _check_tensor(u, "u", shape)
+        if out is None:
+            out = torch.empty_like(u)
+        _check_tensor(out, "out", shape, like=u)
+        _placed(u, out)
+    elif out is None:
         out = torch.empty_like(u)
-    _check_tensor(out, "out", shape, like=u)
-    _placed(u, out)
-    _check(lib().dg_apply_helmholtz(ctypes.byref(desc), _dtype_code(u), float(mass_factor),
-                                    ctypes.c_void_p(u.data_ptr()), ctypes.c_void_p(out.data_ptr()), _stream(u)))
+    _check(lib().dg_apply_helmholtz(desc, _dtype_code(u), float(mass_factor), u.data_ptr(), out.data_ptr(),
+                                    _handle(u)))
     return out
 
 
 def apply_projection(desc, u, tau_d, tau_c, out=None):
     """(M + A_D + A_C) u of the projection step; u: [3, N_el, n^3]; tau_d, tau_c: [N_el]."""
     torch = _torch()
-    shape = (3, _nel(desc), (desc.degree + 1) ** 3)
-    _check_tensor(u, "u", shape)
-    _check_tensor(tau_d, "tau_d", (_nel(desc),), like=u)
-    _check_tensor(tau_c, "tau_c", (_nel(desc),), like=u)
-    if out is None:
+    nel = _nel(desc)
+    shape = (3, nel, (desc.degree + 1) ** 3)
+    if tau_d is None or tau_c is None or not _plain(u, shape, (tau_d, (nel,)), (tau_c, (nel,)), (out, shape)):
+        _check_tensor(u, "u", shape)
+        _check_tensor(tau_d, "tau_d", (nel,), like=u)
+        _check_tensor(tau_c, "tau_c", (nel,), like=u)
+        if out is None:
+            out = torch.empty_like(u)
+        _check_tensor(out, "out", shape, like=u)
+        _placed(u, tau_d, tau_c, out)
+    elif out is None:
         out = torch.empty_like(u)
-    _check_tensor(out, "out", shape, like=u)
-    _placed(u, tau_d, tau_c, out)
-    _check(lib().dg_apply_projection(ctypes.byref(desc), _dtype_code(u), ctypes.c_void_p(u.data_ptr()),
-                                     ctypes.c_void_p(tau_d.data_ptr()), ctypes.c_void_p(tau_c.data_ptr()),
-                                     ctypes.c_void_p(out.data_ptr()), _stream(u)))
+    _check(lib().dg_apply_projection(desc, _dtype_code(u), u.data_ptr(), tau_d.data_ptr(), tau_c.data_ptr(),
+                                     out.data_ptr(), _handle(u)))
     return out
 
 
@@ -409,13 +457,15 @@ def apply_inverse_mass(desc, u, out=None):
     torch = _torch()
     n3 = (desc.degree + 1) ** 3
     shape = (_nel(desc), n3) if desc.n_comp == 1 else (3, _nel(desc), n3)
-    _check_tensor(u, "u", shape)
-    if out is None:
+    if not _plain(u, shape, (out, shape)):
+        _check_tensor(u, "u", shape)
+        if out is None:
+            out = torch.empty_like(u)
+        _check_tensor(out, "out", shape, like=u)
+        _placed(u, out)
+    elif out is None:
         out = torch.empty_like(u)
-    _check_tensor(out, "out", shape, like=u)
-    _placed(u, out)
-    _check(lib().dg_apply_inverse_mass(ctypes.byref(desc), _dtype_code(u), ctypes.c_void_p(u.data_ptr()),
-                                       ctypes.c_void_p(out.data_ptr()), _stream(u)))
+    _check(lib().dg_apply_inverse_mass(desc, _dtype_code(u), u.data_ptr(), out.data_ptr(), _handle(u)))
     return out
 
 
