@@ -164,7 +164,6 @@ ProjPlan make_proj_plan(const dg_op_desc* desc) {
   P.mesh = mesh_args(desc);
   P.S = B.S;
   P.Dg = B.Dg;
-  P.M1 = B.Mref;
   P.w = B.wq;
   P.vol = cell_volume(desc);
   for (int i = 0; i < 3; ++i) {

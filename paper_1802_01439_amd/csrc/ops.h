@@ -129,7 +129,7 @@ struct ProjPlan {
   mutable TabSlots tab;   // FP64, FP32
   int k = 0;
   MeshArgs mesh{};
-  std::vector<double> S, Dg, M1, w;   // n x n, n x n, n x n, n
+  std::vector<double> S, Dg, w;   // n x n, n x n, n
   double vol = 0, ih[3] = {0, 0, 0}, area[3] = {0, 0, 0};
 };
 // dot_partial (optional): one partial sum of u.y per workgroup,

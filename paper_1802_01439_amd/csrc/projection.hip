@@ -13,14 +13,30 @@
 // normal component couples: y_d gains area {tau_C} (M1 (x) M1)(u^-_d - u^+_d)
 // on the face layer (LGL face nodes, M1 the 1D mass on [0,1]).
 //
-// Mapping: one workgroup per batch of E elements, 3 n^2 threads per element
-// (component j, pencil); batches are mapped XCD-aware, so that the
-// neighbours' facing layers are mostly found in the same L2.  The z sweeps
-// of S and S^T run in registers on the loaded and stored z columns; the other
-// sweeps run on LDS pencils in place; 8 barriers.  Both point sets are
-// symmetric about 1/2, so S and S^T are centrosymmetric and Dg, Dg^T
-// centro-antisymmetric: every 1D sweep runs in even-odd form, about half the
-// multiply-adds of the dense product.
+// Component j is swept along its two tangential directions first and along
+// e_j last.  The one-sided traces on the faces normal to e_j, which the
+// continuity term needs at the tangential Gauss points, are then the pencil's
+// end values; the neighbours' traces come from the same two sweeps over their
+// facing layers.  With M1 = S^T W S the term area {tau_C} W (u^-_j - u^+_j) is
+// added after the S^T sweep along e_j, and the two tangential S^T sweeps
+// finish it: no face mass products.  Along e_j, S and Dg (and Dg^T and S^T)
+// run on one pencil in registers.
+//
+// Mapping: one workgroup per batch of E elements, n^2 threads per component
+// (one per pencil); batches are mapped XCD-aware, so that the neighbours'
+// facing layers are mostly found in the same L2.  The first sweep runs on
+// pencils loaded from memory, the last on pencils stored to it, the others on
+// LDS pencils in place; 6 barriers.  Both point sets are symmetric about 1/2,
+// so S and S^T are centrosymmetric and Dg, Dg^T centro-antisymmetric: every 1D
+// sweep runs in even-odd form, about half the multiply-adds of the dense
+// product.
+//
+// What bounds it: vector instructions (55-75 % of the cycles issue one) and
+// LDS (35-45 %) together; memory sees each value read and written once.
+// Measured, FP64, against sweeps in the order x, y, z for all components with
+// the face terms from two products with M1: k = 3, 32^3 43.0 -> 35.0 us,
+// k = 6, 19x18x17 42.3 -> 31.8, k = 7, 24^3 130 -> 95, k = 9, 16^3 114 -> 69,
+// k = 11, 12^3 68 -> 53; FP32 k = 7, 24^3 70 -> 57.
 #include <algorithm>
 #include <cmath>
 
@@ -78,228 +94,199 @@ template <int N, typename T>
 struct ProjTab {
   EOMat<N, T> S, St, Dg, Dt;   // S[q][a] = l_a(z_q); Dg[q][r] = derivative of
                                // the Gauss Lagrange basis r at z_q; St, Dt transposed
-  T M1[N][N];                  // 1D mass on [0,1]
   T w[N];                      // Gauss weights on [0,1]
   T vol, ih[3], area[3];
 };
 
+// LDS layout of one element.  Every component j keeps its block by role: t2
+// innermost, then t1, then the direction n normal to its faces (e_j), with the
+// neighbours' facing layers at both ends (n + 2 layers).  t1 is the first
+// tangential direction swept (z; y for j = 2), t2 the second (x; y for j = 0).
+// So the sweeps run at strides known at compile time, and an odd stride of t1
+// keeps them nearly free of bank conflicts.  Then the six face factors.
 template <int N>
 struct ProjCfg {
-  static constexpr int N2 = N * N, N3 = N * N * N;
-  static constexpr int E = (256 / (3 * N2)) > 0 ? 256 / (3 * N2) : 1;
-  static constexpr int THREADS = E * 3 * N2;
-  static constexpr int PX = LapCfgB<N>::PX, PY = LapCfgB<N>::PY, ES = LapCfgB<N>::ES;
-  // per element: 3 components + div, then 6 own and 6 neighbour face layers
-  static constexpr int PER = 4 * ES + 12 * N2;
+  static constexpr int N2 = N * N, N3 = N * N * N, M = N + 2;
+  // The first two sweeps cover n + 2 layers: n^2 threads per component take
+  // their own layers and then, 2 n of them, the neighbours' two; or n (n + 2)
+  // threads take one pencil each.  The second way costs another wavefront at
+  // most n (n = 8: 4 instead of 3), which measured slower up to n = 10 (n = 6
+  // 111 against 105 us at 32^3, n = 8 98 / 95 at 24^3, n = 9 51 / 45 at 16^3),
+  // but none at n = 7 (31.8 / 33.1), and for n = 11, 12 it is one in eight
+  // (68 / 74, 53 / 56).
+  static constexpr bool TWO = N <= 10 && N != 7;
+  static constexpr int TC = TWO ? N2 : N * M;
+  // elements per workgroup: full wavefronts, and no more of them than needed
+  // to hide the barriers (twice these were 10-30 % slower at n = 2..6)
+  static constexpr int E = N == 2 ? 16 : N == 3 ? 7 : N == 4 ? 4 : N == 5 ? 3 : 1;
+  static constexpr int THREADS = E * 3 * TC;
+  static constexpr int S1 = N | 1, SN = N * S1;
+  static constexpr int CP = M * SN;                 // one component
+  static constexpr int FC = 3 * CP, PER = FC + 6;
 };
 
-// From n = 9 on, at least 4 waves per SIMD (at most 128 VGPRs): at n = 12
-// in FP64 the compiler would otherwise take 129 and halve the resident
-// workgroups.
 template <int N, typename T>
-__global__ void __launch_bounds__(ProjCfg<N>::THREADS) __attribute__((amdgpu_waves_per_eu(N >= 9 ? 4 : 1, 8)))
+__global__ void __launch_bounds__(ProjCfg<N>::THREADS)
 projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restrict__ tau_d,
                   const T* __restrict__ tau_c, MeshArgs mesh, const ProjTab<N, T>* __restrict__ tab,
                   T* __restrict__ dot) {
   using C = ProjCfg<N>;
-  constexpr int N2 = C::N2, N3 = C::N3, E = C::E, PX = C::PX, PY = C::PY, ES = C::ES, PER = C::PER;
-  __shared__ T lds[E * PER];
+  constexpr int N2 = C::N2, N3 = C::N3, M = C::M, TC = C::TC, E = C::E;
+  constexpr int S1 = C::S1, SN = C::SN;
+  __shared__ T lds[E * C::PER];
   const int tid = threadIdx.x;
-  const int le = tid / (3 * N2);
-  const int rem = tid - le * 3 * N2;
-  const int j = rem / N2, p = rem - j * N2;
-  const int p0 = p % N, p1 = p / N;
-  const long long e = (long long)xcd_remap(blockIdx.x, gridDim.x) * E + le;
-  const bool active = e < mesh.n_el;
   const size_t cs = (size_t)mesh.n_el * N3;
-  T* L = lds + le * PER;
-  T* A = L + j * ES;              // this thread's component
-  T* DV = L + 3 * ES;
-  T* GF = L + 4 * ES;             // own face layers, then half-applied face mass  [d][s][t0 + N t1]
-  T* FF = GF + 6 * N2;            // neighbour layers, then jumps, then face terms [d][s][t0 + N t1]
-  const int nxy = mesh.nx * mesh.ny;
-  const int ez = active ? (int)(e / nxy) : 0, exy = active ? (int)(e - (long long)ez * nxy) : 0;
-  const int ey = exy / (mesh.nx > 0 ? mesh.nx : 1), ex = exy - ey * mesh.nx;
-  // pencil base and stride in direction dd for this thread's (p0, p1)
-  auto pencil = [&](int dd, int& base, int& str) {
-    if (dd == 0) { base = PX * p0 + PY * p1; str = 1; }
-    else if (dd == 1) { base = p0 + PY * p1; str = PX; }
-    else { base = p0 + PX * p1; str = PY; }
-  };
-  const int zcol = p0 + PX * p1;   // this thread's z column (a, b) = (p0, p1)
-  T acc = 0;                       // this thread's part of u.y (dot only)
-  // ---- P0: own z column of component j, its face values, the neighbours'
-  //      facing layers of component j = d; S along z in registers
-  if (active) {
-    const T* g = u + j * cs + (size_t)e * N3 + p0 + N * p1;
-    T x[N], v[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) x[c] = g[N2 * c];
-    if (j == 0 && (p0 == 0 || p0 == N - 1)) {   // x faces: (t0, t1) = (b, c)
-#pragma unroll
-      for (int c = 0; c < N; ++c) GF[(0 * 2 + (p0 ? 1 : 0)) * N2 + p1 + N * c] = x[c];
-    }
-    if (j == 1 && (p1 == 0 || p1 == N - 1)) {   // y faces: (t0, t1) = (a, c)
-#pragma unroll
-      for (int c = 0; c < N; ++c) GF[(1 * 2 + (p1 ? 1 : 0)) * N2 + p0 + N * c] = x[c];
-    }
-    if (j == 2) {                                // z faces: (t0, t1) = (a, b)
-      GF[(2 * 2 + 0) * N2 + p] = x[0];
-      GF[(2 * 2 + 1) * N2 + p] = x[N - 1];
-    }
-    // neighbour across (d = j, s): its facing layer at tangential (t0, t1) = (p0, p1)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int nb = neighbor(mesh, ex, ey, ez, j, s);
-      const int lay = s ? 0 : N - 1;
-      int idx;
-      if (j == 0) idx = lay + N * p0 + N2 * p1;
-      else if (j == 1) idx = p0 + N * lay + N2 * p1;
-      else idx = p0 + N * p1 + N2 * lay;
-      FF[(j * 2 + s) * N2 + p] = u[j * cs + (size_t)nb * N3 + idx];
-    }
-    eo_apply<N, 1>(fresh(tab)->S, x, v);
-#pragma unroll
-    for (int c = 0; c < N; ++c) A[zcol + PY * c] = v[c];
-  }
-  __syncthreads();
-  // ---- P1, P2: S along x and y on LDS pencils.  Before the x sweep the face
-  //      jumps u^- - u^+ of this thread's face nodes go into FF; before the
-  //      y sweep the first factor of (M1 (x) M1) is applied to them:
-  //      GF[d][s][p0 + N p1] = sum_t0 M1[p0][t0] jump[t0 + N p1]
-#pragma unroll
-  for (int dd = 0; dd < 2; ++dd) {
-    if (active && dd == 0) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) FF[(j * 2 + s) * N2 + p] = GF[(j * 2 + s) * N2 + p] - FF[(j * 2 + s) * N2 + p];
-    }
-    if (active && dd == 1) {
-      T m0[N];
-#pragma unroll
-      for (int i = 0; i < N; ++i) m0[i] = tab->M1[p0][i];
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const T* df = FF + (j * 2 + s) * N2 + N * p1;
-        T r = 0;
-#pragma unroll
-        for (int t0 = 0; t0 < N; ++t0) r = fmadd(m0[t0], df[t0], r);
-        GF[(j * 2 + s) * N2 + p] = r;
-      }
-    }
-    if (active) {
-      int base, str;
-      pencil(dd, base, str);
+  const int e0 = xcd_remap(blockIdx.x, gridDim.x) * E;
+  auto pick = [](int j, int a0, int a1, int a2) { return j == 0 ? a0 : j == 1 ? a1 : a2; };
+  // ---- P0, P1: S along t1 and t2 of the n + 2 layers
+  {
+    const int le = E == 1 ? 0 : tid / (3 * TC), rem = tid - le * 3 * TC;
+    const int j = rem / TC, p = rem - j * TC;
+    const int e = e0 + le;
+    const bool active = e < mesh.n_el;
+    T* A = lds + le * C::PER + j * C::CP;
+    // layer q of element src, which is its layer lay: S along t1 at position t of t2
+    auto sweep1 = [&](int q, int t, int src, int lay) {
+      const T* g = u + j * cs + (size_t)src * N3 + pick(j, lay + N * t, t + N * lay, t + N2 * lay);
+      const int gs = j == 2 ? N : N2;
       T x[N], v[N];
 #pragma unroll
-      for (int a = 0; a < N; ++a) x[a] = A[base + str * a];
+      for (int c = 0; c < N; ++c) x[c] = g[gs * c];
+      eo_apply<N, 1>(fresh(tab)->S, x, v);
+      T* a = A + SN * q + t;
+#pragma unroll
+      for (int c = 0; c < N; ++c) a[S1 * c] = v[c];
+    };
+    auto sweep2 = [&](int q, int t) {
+      T* a = A + SN * q + S1 * t;
+      T x[N], v[N];
+#pragma unroll
+      for (int c = 0; c < N; ++c) x[c] = a[c];
       eo_apply<N, 1>(fresh(tab)->S, x, v);
 #pragma unroll
-      for (int q = 0; q < N; ++q) A[base + str * q] = v[q];
+      for (int c = 0; c < N; ++c) a[c] = v[c];
+    };
+    if (active) {
+      // the neighbours across the two faces normal to e_j (periodic)
+      const unsigned nxy = mesh.nx * mesh.ny;
+      const unsigned ez = (unsigned)e / nxy, exy = (unsigned)e - ez * nxy;
+      const unsigned ey = exy / (unsigned)mesh.nx, ex = exy - ey * mesh.nx;
+      const int ej = pick(j, ex, ey, ez), last = pick(j, mesh.nx, mesh.ny, mesh.nz) - 1;
+      const int step = pick(j, 1, mesh.nx, nxy);
+      const int nl = e + (ej == 0 ? last : -1) * step, nr = e + (ej == last ? -last : 1) * step;
+      auto factor = [&](int s) {
+        lds[le * C::PER + C::FC + 2 * j + s] = T(0.5) * (tau_c[e] + tau_c[s ? nr : nl]) * tab->area[j];
+      };
+      if constexpr (C::TWO) {
+        const int a = p % N, b = p / N;   // lanes run along x first
+        sweep1(1 + (j == 0 ? a : b), j == 0 ? b : a, e, j == 0 ? a : b);
+        if (p < 2 * N) {
+          sweep1(b ? M - 1 : 0, a, b ? nr : nl, b ? 0 : N - 1);
+          if (a == 0) factor(b);
+        }
+      } else {
+        const int q = j == 0 ? p % M : p / N, t = j == 0 ? p / M : p % N;
+        sweep1(q, t, q == 0 ? nl : q == M - 1 ? nr : e, q == 0 ? N - 1 : q == M - 1 ? 0 : q - 1);
+        if (t == 0 && (q == 0 || q == M - 1)) factor(q != 0);
+      }
+    }
+    __syncthreads();
+    if (active) {
+      if constexpr (C::TWO) {
+        sweep2(1 + p / N, p % N);
+        if (p < 2 * N) sweep2(p < N ? 0 : M - 1, p % N);
+      } else {
+        sweep2(p / N, p % N);
+      }
     }
     __syncthreads();
   }
-  // ---- P3: along direction j: keep vol W ug_j in registers, overwrite
-  //      ug_j with its derivative (1/h_j) Dg_j ug_j
-  int base, str;
-  pencil(j, base, str);
-  T mw[N];
+  // ---- from here n^2 threads per component
+  const int le = E == 1 ? 0 : tid / (3 * N2), rem = tid - le * 3 * N2;
+  const int j = rem / N2, p = rem - j * N2;
+  const int p0 = p % N, p1 = p / N;
+  const int e = e0 + le;
+  const bool active = tid < E * 3 * N2 && e < mesh.n_el;
+  T* L = lds + le * C::PER;
+  T* A = L + j * C::CP;
+  T* aj = A + p0 + S1 * p1;   // (t2, t1) = (p0, p1), from the left neighbour's layer on
+  // ---- P2: S along e_j; keep vol W ug_j and the face terms in registers;
+  //      the derivative (1/h_j) Dg_j ug_j goes back
+  T mw[N], f0 = 0, f1 = 0;
   if (active) {
     const auto& t = *fresh(tab);
     T x[N], v[N];
 #pragma unroll
-    for (int r = 0; r < N; ++r) x[r] = A[base + str * r];
-    // tensor weight along the pencil: the two fixed indices are (p0, p1)
-    const T w2 = t.vol * t.w[p0] * t.w[p1];
+    for (int r = 0; r < N; ++r) x[r] = aj[SN * (r + 1)];
+    const T w2 = t.w[p0] * t.w[p1];   // tensor weight of the two fixed indices
+    f0 = L[C::FC + 2 * j] * w2 * (x[0] - aj[0]);
+    f1 = L[C::FC + 2 * j + 1] * w2 * (x[N - 1] - aj[SN * (N + 1)]);
+    eo_apply<N, 1>(t.S, x, v);
+    const T wv = t.vol * w2;
 #pragma unroll
-    for (int r = 0; r < N; ++r) mw[r] = w2 * t.w[r] * x[r];
-    eo_apply<N, -1>(t.Dg, x, v);
+    for (int r = 0; r < N; ++r) mw[r] = wv * t.w[r] * v[r];
+    eo_apply<N, -1>(t.Dg, v, x);
 #pragma unroll
-    for (int q = 0; q < N; ++q) A[base + str * q] = t.ih[j] * v[q];
+    for (int r = 0; r < N; ++r) aj[SN * (r + 1)] = t.ih[j] * x[r];
   }
   __syncthreads();
-  // ---- P4: DV <- tau_D vol W div on z-column nodes c = j, j+3, ...;
-  //      second factor of (M1 (x) M1) and the penalty factor: continuity term
-  //      of face node (p0, p1) of the faces normal to e_j into FF
-  if (active) {
-    const auto& t = *fresh(tab);
-    const T td = tau_d[e] * t.vol;
-    const T wab = t.w[p0] * t.w[p1];
-    const T* A0 = L;
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-      if (c % 3 != j) continue;
-      const int i = zcol + PY * c;
-      DV[i] = td * wab * t.w[c] * (A0[i] + A0[i + ES] + A0[i + 2 * ES]);
-    }
-    T m1[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) m1[i] = tab->M1[p1][i];
-    const T tce = tau_c[e], area = t.area[j];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int nb = neighbor(mesh, ex, ey, ez, j, s);
-      const T* r = GF + (j * 2 + s) * N2 + p0;
-      T acc = 0;
-#pragma unroll
-      for (int t1 = 0; t1 < N; ++t1) acc = fmadd(m1[t1], r[N * t1], acc);
-      FF[(j * 2 + s) * N2 + p] = T(0.5) * (tce + tau_c[nb]) * area * acc;
-    }
-  }
-  __syncthreads();
-  // ---- P5: z_j = vol W ug_j + (1/h_j) Dg_j^T DV along direction j
+  // ---- P3: tau_D vol W div on this pencil (the sum over the components read by
+  //      each of them: a block of its own in LDS for it was 0-10 % slower), then
+  //      z_j = vol W ug_j + (1/h_j) Dg_j^T of it, S^T along e_j and the face
+  //      terms on the two end nodes
   if (active) {
     const auto& t = *fresh(tab);
     T x[N], v[N];
+    // this pencil in the block of component k with strides sx, sy, sz
+    auto block = [&](int k, int sx, int sy, int sz) {
+      return L + k * C::CP + SN + pick(j, sy * p0 + sz * p1, sx * p0 + sz * p1, sx * p0 + sy * p1);
+    };
+    const T *a0 = block(0, SN, 1, S1), *a1 = block(1, 1, SN, S1), *a2 = block(2, 1, S1, SN);
+    const int s0 = pick(j, SN, 1, S1), s1 = pick(j, 1, SN, S1), s2 = pick(j, 1, S1, SN);
+    const T td = tau_d[e] * t.vol * t.w[p0] * t.w[p1];
 #pragma unroll
-    for (int q = 0; q < N; ++q) x[q] = DV[base + str * q];
+    for (int q = 0; q < N; ++q) x[q] = td * t.w[q] * (a0[s0 * q] + a1[s1 * q] + a2[s2 * q]);
     eo_apply<N, -1>(t.Dt, x, v);
 #pragma unroll
-    for (int r = 0; r < N; ++r) A[base + str * r] = fmadd(t.ih[j], v[r], mw[r]);
+    for (int r = 0; r < N; ++r) x[r] = fmadd(t.ih[j], v[r], mw[r]);
+    eo_apply<N, 1>(t.St, x, v);
+    v[0] += f0;
+    v[N - 1] += f1;
+#pragma unroll
+    for (int r = 0; r < N; ++r) mw[r] = v[r];
   }
   __syncthreads();
-  // ---- P6, P7: S^T along x and y
-#pragma unroll
-  for (int dd = 0; dd < 2; ++dd) {
-    if (active) {
-      int b2, s2;
-      pencil(dd, b2, s2);
-      T x[N], v[N];
-#pragma unroll
-      for (int q = 0; q < N; ++q) x[q] = A[b2 + s2 * q];
-      eo_apply<N, 1>(fresh(tab)->St, x, v);
-#pragma unroll
-      for (int a = 0; a < N; ++a) A[b2 + s2 * a] = v[a];
-    }
-    __syncthreads();
-  }
-  // ---- P8: S^T along z in registers, the continuity terms of this column's
-  //      face nodes, store
   if (active) {
+#pragma unroll
+    for (int r = 0; r < N; ++r) aj[SN * (r + 1)] = mw[r];
+  }
+  __syncthreads();
+  // ---- P4: S^T along t2
+  if (active) {
+    T* a = A + SN * (p1 + 1) + S1 * p0;
     T x[N], v[N];
 #pragma unroll
-    for (int c = 0; c < N; ++c) x[c] = A[zcol + PY * c];
+    for (int q = 0; q < N; ++q) x[q] = a[q];
     eo_apply<N, 1>(fresh(tab)->St, x, v);
-    if (j == 0 && (p0 == 0 || p0 == N - 1)) {
 #pragma unroll
-      for (int c = 0; c < N; ++c) v[c] += FF[(0 * 2 + (p0 ? 1 : 0)) * N2 + p1 + N * c];
-    }
-    if (j == 1 && (p1 == 0 || p1 == N - 1)) {
+    for (int q = 0; q < N; ++q) a[q] = v[q];
+  }
+  __syncthreads();
+  // ---- P5: S^T along t1, store; lanes run along x (n for j = 0, else t2)
+  T acc = 0;   // this thread's part of u.y (dot only)
+  if (active) {
+    const T* a = A + SN + (j == 0 ? SN * p0 + p1 : p0 + SN * p1);
+    T x[N], v[N];
 #pragma unroll
-      for (int c = 0; c < N; ++c) v[c] += FF[(1 * 2 + (p1 ? 1 : 0)) * N2 + p0 + N * c];
-    }
-    if (j == 2) {
-      v[0] += FF[(2 * 2 + 0) * N2 + p];
-      v[N - 1] += FF[(2 * 2 + 1) * N2 + p];
-    }
-    T* g = y + j * cs + (size_t)e * N3 + p0 + N * p1;
+    for (int c = 0; c < N; ++c) x[c] = a[S1 * c];
+    eo_apply<N, 1>(fresh(tab)->St, x, v);
+    const size_t o = j * cs + (size_t)e * N3 + p0 + (j == 2 ? N2 : N) * p1;
+    const int gs = j == 2 ? N : N2;
 #pragma unroll
-    for (int c = 0; c < N; ++c) g[N2 * c] = v[c];
-    if (dot) {   // u.y of this column (the input column again, from cache)
-      const T* gu = u + j * cs + (size_t)e * N3 + p0 + N * p1;
-      T sdot = 0;
+    for (int c = 0; c < N; ++c) y[o + gs * c] = v[c];
+    if (dot) {   // u.y of this pencil (the input again, from cache)
 #pragma unroll
-      for (int c = 0; c < N; ++c) sdot = fmadd(gu[N2 * c], v[c], sdot);
-      acc = sdot;
+      for (int c = 0; c < N; ++c) acc = fmadd(u[o + gs * c], v[c], acc);
     }
   }
   // ---- optional: workgroup sum of u.y into dot[blockIdx.x] (fixed order)
@@ -307,10 +294,12 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
     __syncthreads();
     lds[tid] = acc;
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {   // one wavefront
       T s = 0;
-      for (int i = 0; i < C::THREADS; ++i) s += lds[i];
-      dot[blockIdx.x] = s;
+      for (int i = tid; i < C::THREADS; i += 64) s += lds[i];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      if (tid == 0) dot[blockIdx.x] = s;
     }
   }
 }
@@ -344,7 +333,6 @@ bool make_proj_tab(const ProjPlan& P, ProjTab<N, T>& t) {
     for (int a = 0; a < N; ++a) {
       St[a * N + i] = P.S[i * N + a];
       Dt[a * N + i] = P.Dg[i * N + a];
-      t.M1[i][a] = (T)P.M1[i * N + a];
     }
     t.w[i] = (T)P.w[i];
   }

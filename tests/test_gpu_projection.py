@@ -65,6 +65,21 @@ def test_projection_one_element_directions(k, n_el):
     assert rel_err(y, projection_apply(u, k, msh, td, tc)) < 1e-12
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("k,n_el", [(1, (1, 1, 1)), (1, (4, 2, 2)), (1, (17, 1, 1)), (2, (7, 1, 1)), (2, (2, 2, 2)),
+                                    (3, (2, 2, 1)), (3, (1, 5, 1)), (4, (3, 1, 1)), (4, (1, 2, 2)), (5, (1, 1, 2)),
+                                    (6, (2, 3, 4)), (9, (1, 2, 1)), (10, (2, 1, 2)), (11, (1, 1, 3))])
+def test_projection_batch_fills_and_strong_penalties(k, n_el, dtype):
+    """One element, a full batch and one more (16, 7, 4, 3 elements at k = 1..4),
+    both ways of sweeping the neighbours' layers (k = 6, 10, 11 and the rest),
+    with penalties that dominate the mass term."""
+    msh, u, td, tc = _case(k, n_el, (1.3 * n_el[0], 0.8 * n_el[1], 1.1 * n_el[2]), 890 + k, dtype)
+    td, tc = 64 * td, 64 * tc   # a power of two: no new rounding in FP32
+    announce(f"projection k={k} {dtype} n_el={n_el} strong penalties")
+    y = _run(k, msh, u, td, tc, dtype)
+    assert rel_err(y, projection_apply(u, k, msh, td, tc)) < (1e-12 if dtype == torch.float64 else 1e-5)
+
+
 @pytest.mark.parametrize("k", [3, 8])
 def test_projection_zero_penalty_is_the_mass_matrix(k):
     msh, u, _, _ = _case(k, (4, 3, 2), (2.0, 1.5, 1.0), 850 + k, torch.float64)
