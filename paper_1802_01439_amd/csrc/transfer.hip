@@ -21,7 +21,8 @@
 // column is then read by each of them (from L2: they run on one XCD).  Restriction: per child a z sweep from the child's
 // column, a y sweep in LDS, and an x sweep whose result each thread
 // accumulates in registers for its own x pencil of the coarse element
-// (3 barriers per child).
+// (3 barriers per child); on few coarse elements a second kernel runs the
+// children side by side instead.
 #include "api_internal.h"
 #include "common.h"
 #include "laplace_kernels.h"
@@ -227,6 +228,133 @@ restrict_kernel(const T* __restrict__ rf, T* __restrict__ rc, LevelArgs lv,
   }
 }
 
+// The restriction on few coarse elements: CG children of a batch at a time
+// (all eight up to n = 11), each on W wavefronts of its own, so that a child's
+// matrices are uniform there and read by scalar loads.  restrict_kernel's
+// chain of 24 phases, each waiting for the last, becomes one of 3 (6 at
+// n = 12); the children's results are summed from LDS in the same order.
+template <int N>
+struct RestrictWideCfg {
+  static constexpr int N2 = N * N, N3 = N * N * N;
+  static constexpr int E = N2 < 64 ? 64 / N2 : 1;
+  static constexpr int W = (E * N2 + 63) / 64;
+  static constexpr int CG = 8 * W * 64 <= 1024 ? 8 : 4;
+  static constexpr int THREADS = CG * W * 64;
+  // Taken up to this many workgroups of restrict_kernel.  Measured, this one
+  // against the loop, us: k = 7 FP32 3^3 6.4 / 10.8 (launch bound), 12^3 (432)
+  // 10.1 / 14.4; k = 11 FP64 5^3 (125) 12.2 / 23.7; k = 4 16^3 (410) 8.9 / 12.3;
+  // but k = 4 25^3 (1563) 21.0 / 16.3, k = 10 12^3 (864) 55.6 / 47.8.  Where
+  // n^2 fills its wavefronts badly (n = 6, 9) the loop is even earlier:
+  // k = 8 11^3 (444) 28.5 / 24.7, 8^3 and below this one.
+  static constexpr int GRID_MAX = 4 * E * N2 >= 3 * W * 64 ? 512 : 256;
+  static constexpr int PX = LapCfgB<N>::PX, PY = LapCfgB<N>::PY, ES = LapCfgB<N>::ES;
+};
+
+template <int N, typename T>
+__global__ void __launch_bounds__(RestrictWideCfg<N>::THREADS)
+restrict_wide_kernel(const T* __restrict__ rf, T* __restrict__ rc, LevelArgs lv,
+                const TransferTab<N, T>* __restrict__ tab) {
+  using C = RestrictWideCfg<N>;
+  constexpr int N2 = C::N2, N3 = C::N3, E = C::E, ES = C::ES, PX = C::PX, PY = C::PY;
+  __shared__ T U[C::CG * E * ES];
+  const int tid = threadIdx.x;
+  const int cg = __builtin_amdgcn_readfirstlane(tid >> 6) / C::W;
+  const int lane = tid - cg * C::W * 64;
+  const int le = lane / N2, p = lane - le * N2;
+  const int p0 = p % N, p1 = p / N;
+  const long long e0 = (long long)xcd_remap(blockIdx.x, gridDim.x) * E, e = e0 + le;
+  const bool active = le < E && e < lv.ncoarse;
+  const int comp = blockIdx.y;
+  const int nxf = 2 * lv.nxc, nyf = 2 * lv.nyc;
+  int ex = 0, ey = 0, ez = 0;
+  if (active) {
+    const unsigned nxy = lv.nxc * lv.nyc, ei = (unsigned)e;
+    ez = ei / nxy;
+    const unsigned r = ei - ez * nxy;
+    ey = r / (unsigned)lv.nxc;
+    ex = r - ey * lv.nxc;
+  }
+  T* Ue = U + (cg * E + le) * ES;
+  // this thread's coarse nodes tid, tid + THREADS, ... of the batch
+  constexpr int PER = (E * N3 + C::THREADS - 1) / C::THREADS;
+  T acc[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) acc[i] = 0;
+#pragma unroll
+  for (int c0 = 0; c0 < 8; c0 += C::CG) {
+    const int ch = c0 + cg, cx = ch & 1, cy = (ch >> 1) & 1, cz = ch >> 2;
+    T x[N], y[N];
+    // z: the child's column (i, j) = (p0, p1), P_cz^T
+    if (active) {
+      const long long f = (2 * ex + cx) + (long long)nxf * ((2 * ey + cy) + (long long)nyf * (2 * ez + cz));
+      const T* g = rf + ((size_t)comp * 8 * lv.ncoarse + f) * N3 + p0 + N * p1;
+#pragma unroll
+      for (int l = 0; l < N; ++l) x[l] = g[N2 * l];
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        T s = tab->R[cz][c][0] * x[0];
+#pragma unroll
+        for (int l = 1; l < N; ++l) s = fmadd(tab->R[cz][c][l], x[l], s);
+        y[c] = s;
+      }
+      T* a = Ue + p0 + PX * p1;
+#pragma unroll
+      for (int c = 0; c < N; ++c) a[PY * c] = y[c];
+    }
+    __syncthreads();
+    // y: pencil (i, c) = (p0, p1), P_cy^T, in place
+    if (active) {
+      T* a = Ue + p0 + PY * p1;
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = a[PX * j];
+#pragma unroll
+      for (int b = 0; b < N; ++b) {
+        T s = tab->R[cy][b][0] * x[0];
+#pragma unroll
+        for (int j = 1; j < N; ++j) s = fmadd(tab->R[cy][b][j], x[j], s);
+        y[b] = s;
+      }
+#pragma unroll
+      for (int b = 0; b < N; ++b) a[PX * b] = y[b];
+    }
+    __syncthreads();
+    // x: pencil (b, c) = (p0, p1), P_cx^T, in place
+    if (active) {
+      T* a = Ue + PX * p0 + PY * p1;
+#pragma unroll
+      for (int i = 0; i < N; ++i) x[i] = a[i];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        T s = tab->R[cx][i][0] * x[0];
+#pragma unroll
+        for (int l = 1; l < N; ++l) s = fmadd(tab->R[cx][i][l], x[l], s);
+        y[i] = s;
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) a[i] = y[i];
+    }
+    __syncthreads();
+    // the sum over the children
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int k = tid + i * C::THREADS;
+      if (k < E * N3) {
+        const int m = k / N3, q = k - m * N3, c = q / N2, ab = q - c * N2, b = ab / N;
+        const T* a = U + m * ES + (ab - b * N) + PX * b + PY * c;
+#pragma unroll
+        for (int g = 0; g < C::CG; ++g) acc[i] += a[g * E * ES];
+      }
+    }
+    if (C::CG < 8) __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int k = tid + i * C::THREADS;
+    if (k < E * N3 && e0 + k / N3 < lv.ncoarse)
+      rc[((size_t)comp * lv.ncoarse + e0) * N3 + k] = acc[i];
+  }
+}
+
 template <int N, typename T, bool ACC>
 hipError_t launch_prolong(const TransferPlan& P, const void* src, void* dst, long long grid, const TransferTab<N, T>* dt,
                           LevelArgs lv, hipStream_t s) {
@@ -259,8 +387,13 @@ hipError_t launch_n(const TransferPlan& P, int mode, const void* src, void* dst,
   if (grid == 0) return hipSuccess;
   if (mode == 1) return launch_prolong<N, T, false>(P, src, dst, grid, dt, lv, s);
   if (mode == 2) return launch_prolong<N, T, true>(P, src, dst, grid, dt, lv, s);
-  hipLaunchKernelGGL((restrict_kernel<N, T>), dim3((unsigned)grid, (unsigned)P.n_comp), dim3(C::THREADS), 0, s,
-                     (const T*)src, (T*)dst, lv, dt);
+  using W = RestrictWideCfg<N>;
+  if (grid * P.n_comp <= W::GRID_MAX)
+    hipLaunchKernelGGL((restrict_wide_kernel<N, T>), dim3((unsigned)((lv.ncoarse + W::E - 1) / W::E), (unsigned)P.n_comp),
+                       dim3(W::THREADS), 0, s, (const T*)src, (T*)dst, lv, dt);
+  else
+    hipLaunchKernelGGL((restrict_kernel<N, T>), dim3((unsigned)grid, (unsigned)P.n_comp), dim3(C::THREADS), 0, s,
+                       (const T*)src, (T*)dst, lv, dt);
   return hipGetLastError();
 }
 

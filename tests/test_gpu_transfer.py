@@ -93,3 +93,19 @@ def test_transfer_parity_serial_children(k, n_el, n_comp, dtype):
     assert rel_err(uf, prolongate(uc, k, coarse)) < tol
     rc = dgmf.restrict(d, to_dev(rf, dtype)).double().cpu().numpy()
     assert rel_err(rc, restrict(rf, k, coarse)) < tol
+
+
+@pytest.mark.parametrize("k,n_el,dtype", [(1, (33, 32, 32), torch.float64), (2, (25, 24, 24), torch.float32),
+                                          (5, (16, 15, 15), torch.float64), (8, (7, 11, 10), torch.float64),
+                                          (8, (7, 11, 10), torch.float32), (11, (9, 15, 4), torch.float64)])
+def test_restriction_loop_over_the_children(k, n_el, dtype):
+    """Coarse meshes above the size up to which the children run side by side
+    (test_transfer_parity's are below it at every degree)."""
+    coarse = M.Mesh(n_el, (1.0, 0.8, 1.2))
+    rf = inputs.uniform((8 * coarse.N, (k + 1) ** 3), seed=1100 + k)
+    if dtype == torch.float32:
+        rf = round_f32(rf)
+    d = dgmf.make_desc(k, n_el, tuple(coarse.length))
+    announce(f"restriction loop k={k} {dtype} coarse={n_el}")
+    rc = dgmf.restrict(d, to_dev(rf, dtype)).double().cpu().numpy()
+    assert rel_err(rc, restrict(rf, k, coarse)) < (1e-12 if dtype == torch.float64 else 1e-5)
