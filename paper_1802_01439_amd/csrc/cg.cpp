@@ -358,12 +358,12 @@ int cg_run(const dg_op_desc* desc, const dg_cg_opts* opts, const double* b, doub
   S.ok(cg_fill(W.p, 0.0, n, S.s));
   if (cheb) S.ok(cg_fill32(Zb[1], 0.0f, n, S.s));
   const int napp = cheb ? opts->cheb_degree - 1 : 0;
-  // scalars of the current residual (sums of r from the x/r update), then
+  // scalars of the current residual (sums of r from the r update), then
   // z = M^-1 r' with the sums of the flexible beta
   auto precondition = [&](bool start) {
     if (!cheb) {
       S.ok(cg_fin_jacobi(W.partial, W.st, start, S.s));
-      S.ok(cg_update_p_jacobi(W.r, W.p, W.dinv, S.n3, W.st, n, S.s));
+      S.ok(cg_update_p_jacobi(W.r, W.p, x, W.dinv, S.n3, W.st, n, S.s));
       return;
     }
     S.ok(cg_fin_resid(W.partial, W.st, start, S.s));
@@ -391,11 +391,11 @@ int cg_run(const dg_op_desc* desc, const dg_cg_opts* opts, const double* b, doub
       rho_prev = rho;
     }
     S.ok(cg_fin_cheb(W.partial, napp == 0 ? kCgBlocks : (int)grid32, W.st, start, S.s));
-    S.ok(cg_update_p_cheb(Zb[zn], W.p, W.st, n, S.s));
+    S.ok(cg_update_p_z(Zb[zn], W.p, x, W.st, n, S.s));
     zn = 1 - zn;
   };
   // start: alpha is 0 in the fresh state, so this only forms the sums of r0
-  S.ok(cg_update_xr_st(x, W.r, W.p, W.q, W.dinv, S.n3, W.st, !cheb, n, W.partial, S.s));
+  S.ok(cg_update_r_st(W.r, W.q, W.dinv, S.n3, W.st, !cheb, n, W.partial, S.s));
   precondition(true);
   // batch size: up to max_batch, fewer when the observed contraction rate
   // says the tolerance is that close (keeps queued no-op iterations rare)
@@ -422,7 +422,7 @@ int cg_run(const dg_op_desc* desc, const dg_cg_opts* opts, const double* b, doub
       ++S.matvec64;
       S.ok(cg_apply_dot(LP, W.p, W.q, W.partial, S.s, tabs.f64));
       S.ok(cg_fin_alpha(W.partial, (int)grid64, W.st, S.s));
-      S.ok(cg_update_xr_st(x, W.r, W.p, W.q, W.dinv, S.n3, W.st, !cheb, n, W.partial, S.s));
+      S.ok(cg_update_r_st(W.r, W.q, W.dinv, S.n3, W.st, !cheb, n, W.partial, S.s));
       precondition(false);
     }
     queued += batch;

@@ -46,34 +46,36 @@ hipError_t cg_xpby(double* y, const double* x, double b, long long n, hipStream_
 // main loop with device-side scalars
 hipError_t cg_state_init(double* st, double tol2, int max_it, double sum_d, long long n, bool proj, hipStream_t s);
 hipError_t cg_fin_alpha(const double* partial, int nblocks, double* st, hipStream_t s);
-hipError_t cg_update_xr_st(double* x, double* r, const double* p, const double* q, const double* dinv, int n3,
-                           const double* st, bool jacobi, long long n, double* partial, hipStream_t s);
+// r -= alpha q with the sums of r; the direction updates below also do
+// x += alpha p with the old direction
+hipError_t cg_update_r_st(double* r, const double* q, const double* dinv, int n3, const double* st, bool jacobi,
+                          long long n, double* partial, hipStream_t s);
 hipError_t cg_fin_jacobi(const double* partial, double* st, bool start, hipStream_t s);
 hipError_t cg_fin_resid(const double* partial, double* st, bool start, hipStream_t s);
 hipError_t cg_fin_cheb(const double* partial, int nblocks, double* st, bool start, hipStream_t s);
 hipError_t cg_cheb1(const double* r, float* z, const float* zprev, const float* dinv32, int n3, const double* st,
                     float inv_theta, long long n, double* partial, hipStream_t s);
 hipError_t cg_fill32(float* y, float c, long long n, hipStream_t s);
-hipError_t cg_update_p_jacobi(const double* r, double* p, const double* dinv, int n3, const double* st, long long n,
-                              hipStream_t s);
-hipError_t cg_update_p_cheb(const float* z, double* p, const double* st, long long n, hipStream_t s);
+hipError_t cg_update_p_jacobi(const double* r, double* p, double* x, const double* dinv, int n3, const double* st,
+                              long long n, hipStream_t s);
 
 // a preconditioner that is a separate call (the V-cycle), in FP64 or FP32:
 // its input r' = r - mu_r, the partials of the flexible beta (for
-// cg_fin_cheb with kCgBlocks), and p = (z - mu_z) + beta p
+// cg_fin_cheb with kCgBlocks), and x += alpha p, p = (z - mu_z) + beta p
 hipError_t cg_rprime(const double* r, const double* st, double* out, long long n, hipStream_t s);
 hipError_t cg_rprime(const double* r, const double* st, float* out, long long n, hipStream_t s);
 hipError_t cg_zsums(const double* r, const double* z, const double* zprev, const double* st, long long n,
                     double* partial, hipStream_t s);
 hipError_t cg_zsums(const double* r, const float* z, const float* zprev, const double* st, long long n,
                     double* partial, hipStream_t s);
-hipError_t cg_update_p_z(const double* z, double* p, const double* st, long long n, hipStream_t s);
-hipError_t cg_update_p_z(const float* z, double* p, const double* st, long long n, hipStream_t s);
+hipError_t cg_update_p_z(const double* z, double* p, double* x, const double* st, long long n, hipStream_t s);
+hipError_t cg_update_p_z(const float* z, double* p, double* x, const double* st, long long n, hipStream_t s);
 
 // inverse-mass-preconditioned CG with device-side scalars (same state layout)
 hipError_t mpcg_start(const double* partial, double* st, hipStream_t s);
-hipError_t mpcg_beta(const double* rr_partial, const double* rz_partial, int nblocks, double* st, hipStream_t s);
-hipError_t mpcg_xpby(double* p, const double* z, const double* st, long long n, hipStream_t s);
+hipError_t mpcg_beta(const double* partial, int nblocks, double* st, hipStream_t s);   // sums r.r, r.z
+// x += alpha p, p = z + beta p
+hipError_t mpcg_update_xp(double* x, double* p, const double* z, const double* st, long long n, hipStream_t s);
 
 // multigrid V-cycle: a Chebyshev smoother of one step, x = s D^-1 b, and
 // vector updates (FP64, FP32)

@@ -4,6 +4,8 @@
 // Chebyshev preconditioner's vectors are FP32.
 #include "cg_kernels.h"
 
+#include "cg_sums.h"
+
 namespace dgmf {
 
 namespace {
@@ -30,21 +32,14 @@ __device__ __forceinline__ void block_partials(double (&v)[NQ], double* partial)
   }
 }
 
-__global__ void __launch_bounds__(kThreads) k_finalize(const double* __restrict__ partial, int nblocks, int nq,
-                                                       double* __restrict__ out) {
-  __shared__ double sh[kThreads];
-  for (int q = 0; q < nq; ++q) {
-    double s = 0;
-    for (int i = threadIdx.x; i < nblocks; i += kThreads) s += partial[q * nblocks + i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = kThreads / 2; st > 0; st >>= 1) {
-      if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[q] = sh[0];
-    __syncthreads();
-  }
+template <int NQ>
+__global__ void __launch_bounds__(kSumThreads) k_finalize(const double* __restrict__ partial, int nblocks,
+                                                          double* __restrict__ out) {
+  double v[NQ];
+  block_sums<NQ>(partial, nblocks, v);
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) out[q] = v[q];
 }
 
 // r = b - q; partials: sum r, sum r^2, sum b, sum b^2
@@ -170,37 +165,8 @@ __global__ void __launch_bounds__(kThreads) k_fill(double* __restrict__ y, doubl
 // S_rdr = sum d r^2 (S_d = sum d is a setup constant).  r itself is stored
 // unprojected; every use subtracts mu.
 
-// Sums of partial[q * nblocks + i] over i for q < NQ, in a fixed order
-// (thread-strided, then across the wavefront, then across the 4 wavefronts);
-// valid in thread 0.
-template <int NQ>
-__device__ __forceinline__ void block_sums(const double* __restrict__ partial, int nblocks, double (&out)[NQ]) {
-  static_assert(kThreads == 256, "four full wavefronts");
-  __shared__ double sh[NQ][kThreads / 64];
-  double s[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) s[q] = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += kThreads) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) s[q] += partial[(size_t)q * nblocks + i];
-  }
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o, 64);
-  }
-  const int w = threadIdx.x / 64;
-  if (threadIdx.x % 64 == 0) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) sh[q][w] = s[q];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) out[q] = ((sh[q][0] + sh[q][1]) + sh[q][2]) + sh[q][3];
-}
-
 // alpha = rz / p.q  (p.q from one partial), breakdown if p.q <= 0 or not finite
-__global__ void __launch_bounds__(kThreads) k_fin_alpha(const double* __restrict__ partial, int nblocks,
+__global__ void __launch_bounds__(kSumThreads) k_fin_alpha(const double* __restrict__ partial, int nblocks,
                                                         double* __restrict__ st) {
   double v[1];
   block_sums<1>(partial, nblocks, v);
@@ -220,19 +186,19 @@ __global__ void __launch_bounds__(kThreads) k_fin_alpha(const double* __restrict
   st[kAlpha] = st[kRZ] / pq;
 }
 
-// x += alpha p; r -= alpha q; partials S_r, S_rr and (JAC) S_dr, S_rdr
+// r -= alpha q; partials S_r, S_rr and (JAC) S_dr, S_rdr.  x += alpha p is
+// left to the direction update, which reads p anyway: one vector less per
+// iteration.
 template <bool JAC>
-__global__ void __launch_bounds__(kThreads) k_update_xr_st(double* __restrict__ x, double* __restrict__ r,
-                                                           const double* __restrict__ p, const double* __restrict__ q,
-                                                           const double* __restrict__ dinv, int n3,
-                                                           const double* __restrict__ st, long long n,
-                                                           double* partial) {
+__global__ void __launch_bounds__(kThreads) k_update_r_st(double* __restrict__ r, const double* __restrict__ q,
+                                                          const double* __restrict__ dinv, int n3,
+                                                          const double* __restrict__ st, long long n,
+                                                          double* partial) {
   const double alpha = st[kAlpha];
   double v[JAC ? 4 : 2] = {};
   for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
     double ri = r[i];
     if (alpha != 0.0) {
-      x[i] += alpha * p[i];
       ri -= alpha * q[i];
       r[i] = ri;
     }
@@ -245,6 +211,19 @@ __global__ void __launch_bounds__(kThreads) k_update_xr_st(double* __restrict__ 
     }
   }
   block_partials<JAC ? 4 : 2>(v, partial);
+}
+
+// x += alpha p, then p = z + beta p, of entry i (z formed by the caller): a
+// zero alpha touches no x, a zero beta never reads the old direction for p
+__device__ __forceinline__ void step_xp(double* __restrict__ x, double* __restrict__ p, long long i, double alpha,
+                                        double beta, double zi) {
+  if (alpha != 0.0 || beta != 0.0) {
+    const double pi = p[i];
+    if (alpha != 0.0) x[i] += alpha * pi;
+    p[i] = beta != 0.0 ? zi + beta * pi : zi;
+  } else {
+    p[i] = zi;
+  }
 }
 
 // count the iteration (not for the start) and test convergence / limits
@@ -263,7 +242,7 @@ __device__ void account(double* st, double rn2, double rz, bool start) {
 
 // Jacobi: scalars of the new residual (sums from k_update_xr_st<true>);
 // beta = rz_new / rz (a fixed symmetric preconditioner: standard PCG)
-__global__ void __launch_bounds__(kThreads) k_fin_jacobi(const double* __restrict__ partial, int nblocks,
+__global__ void __launch_bounds__(kSumThreads) k_fin_jacobi(const double* __restrict__ partial, int nblocks,
                                                          double* __restrict__ st, int start) {
   double v[4];
   block_sums<4>(partial, nblocks, v);
@@ -286,7 +265,7 @@ __global__ void __launch_bounds__(kThreads) k_fin_jacobi(const double* __restric
 
 
 // Chebyshev: mean and norm of the new residual (sums from k_update_xr_st<false>)
-__global__ void __launch_bounds__(kThreads) k_fin_resid(const double* __restrict__ partial, int nblocks,
+__global__ void __launch_bounds__(kSumThreads) k_fin_resid(const double* __restrict__ partial, int nblocks,
                                                         double* __restrict__ st, int start) {
   double v[2];
   block_sums<2>(partial, nblocks, v);
@@ -302,25 +281,13 @@ __global__ void __launch_bounds__(kThreads) k_fin_resid(const double* __restrict
   account(st, rn2, 1.0, start != 0);
 }
 
-// p = D^-1 (r - mu) - mu_z + beta p
+// x += alpha p, p = D^-1 (r - mu) - mu_z + beta p
 __global__ void __launch_bounds__(kThreads) k_update_p_jacobi(const double* __restrict__ r, double* __restrict__ p,
-                                                              const double* __restrict__ dinv, int n3,
-                                                              const double* __restrict__ st, long long n) {
-  const double mu = st[kMuR], muz = st[kMuZ], beta = st[kBeta];
-  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
-    const double zi = fma(dinv[i % n3], r[i] - mu, -muz);
-    p[i] = beta != 0.0 ? zi + beta * p[i] : zi;   // a zero beta never reads the old direction
-  }
-}
-
-// p = (z - mu_z) + beta p, z the FP32 smoother output
-__global__ void __launch_bounds__(kThreads) k_update_p_cheb(const float* __restrict__ z, double* __restrict__ p,
-                                                            const double* __restrict__ st, long long n) {
-  const double muz = st[kMuZ], beta = st[kBeta];
-  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
-    const double zi = (double)z[i] - muz;
-    p[i] = beta != 0.0 ? zi + beta * p[i] : zi;
-  }
+                                                              double* __restrict__ x, const double* __restrict__ dinv,
+                                                              int n3, const double* __restrict__ st, long long n) {
+  const double alpha = st[kAlpha], mu = st[kMuR], muz = st[kMuZ], beta = st[kBeta];
+  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads)
+    step_xp(x, p, i, alpha, beta, fma(dinv[i % n3], r[i] - mu, -muz));
 }
 
 // Chebyshev degree 1 (no operator apply): z = D^-1 r' / theta and the
@@ -350,7 +317,7 @@ __global__ void __launch_bounds__(kThreads) k_fill32(float* __restrict__ y, floa
 }
 
 // flexible beta = r'.(z' - zold) / rz with z' = z - mu_z
-__global__ void __launch_bounds__(kThreads) k_fin_cheb(const double* __restrict__ partial, int nblocks,
+__global__ void __launch_bounds__(kSumThreads) k_fin_cheb(const double* __restrict__ partial, int nblocks,
                                                        double* __restrict__ st, int start) {
   double v[3];
   block_sums<3>(partial, nblocks, v);
@@ -371,7 +338,8 @@ __global__ void __launch_bounds__(kThreads) k_fin_cheb(const double* __restrict_
 // Preconditioners that are a separate call (the multigrid V-cycle): the
 // cycle's input r' = r - mu_r in the cycle's precision, the partials sum z,
 // r'.z, r'.(zprev - mu_z_prev) of the flexible beta (k_fin_cheb), and
-// p = (z - mu_z) + beta p, for an output z in either precision.
+// x += alpha p, p = (z - mu_z) + beta p, for an output z in either precision
+// (also the FP32 Chebyshev smoother's).
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_rprime(const double* __restrict__ r, const double* __restrict__ st,
                                                      T* __restrict__ out, long long n) {
@@ -397,12 +365,11 @@ __global__ void __launch_bounds__(kThreads) k_zsums(const double* __restrict__ r
 
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_update_p_z(const T* __restrict__ z, double* __restrict__ p,
-                                                         const double* __restrict__ st, long long n) {
-  const double muz = st[kMuZ], beta = st[kBeta];
-  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
-    const double zi = (double)z[i] - muz;
-    p[i] = beta != 0.0 ? zi + beta * p[i] : zi;   // a zero beta never reads the old direction
-  }
+                                                         double* __restrict__ x, const double* __restrict__ st,
+                                                         long long n) {
+  const double alpha = st[kAlpha], muz = st[kMuZ], beta = st[kBeta];
+  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads)
+    step_xp(x, p, i, alpha, beta, (double)z[i] - muz);
 }
 
 // state set-up: zero, then the constants
@@ -428,7 +395,11 @@ __global__ void k_state_init(double* __restrict__ st, double tol2, double max_it
   } while (0)
 
 hipError_t cg_finalize(const double* partial, int nq, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), 0, s, partial, kCgBlocks, nq, out);
+  switch (nq) {
+    case 1: hipLaunchKernelGGL(k_finalize<1>, dim3(1), dim3(kSumThreads), 0, s, partial, kCgBlocks, out); break;
+    case 4: hipLaunchKernelGGL(k_finalize<4>, dim3(1), dim3(kSumThreads), 0, s, partial, kCgBlocks, out); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 hipError_t cg_residual(const double* b, const double* q, double* r, long long n, double* partial, hipStream_t s) {
@@ -463,24 +434,25 @@ hipError_t cg_state_init(double* st, double tol2, int max_it, double sum_d, long
   return hipGetLastError();
 }
 hipError_t cg_fin_alpha(const double* partial, int nblocks, double* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kThreads), 0, s, partial, nblocks, st);
+  hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st);
   return hipGetLastError();
 }
-hipError_t cg_update_xr_st(double* x, double* r, const double* p, const double* q, const double* dinv, int n3,
-                           const double* st, bool jacobi, long long n, double* partial, hipStream_t s) {
-  if (jacobi) DG_LAUNCH(k_update_xr_st<true>, x, r, p, q, dinv, n3, st, n, partial);
-  DG_LAUNCH(k_update_xr_st<false>, x, r, p, q, dinv, n3, st, n, partial);
+hipError_t cg_update_r_st(double* r, const double* q, const double* dinv, int n3, const double* st, bool jacobi,
+                          long long n, double* partial, hipStream_t s) {
+  if (jacobi) DG_LAUNCH(k_update_r_st<true>, r, q, dinv, n3, st, n, partial);
+  DG_LAUNCH(k_update_r_st<false>, r, q, dinv, n3, st, n, partial);
 }
+
 hipError_t cg_fin_jacobi(const double* partial, double* st, bool start, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_jacobi, dim3(1), dim3(kThreads), 0, s, partial, kCgBlocks, st, start ? 1 : 0);
+  hipLaunchKernelGGL(k_fin_jacobi, dim3(1), dim3(kSumThreads), 0, s, partial, kCgBlocks, st, start ? 1 : 0);
   return hipGetLastError();
 }
 hipError_t cg_fin_resid(const double* partial, double* st, bool start, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_resid, dim3(1), dim3(kThreads), 0, s, partial, kCgBlocks, st, start ? 1 : 0);
+  hipLaunchKernelGGL(k_fin_resid, dim3(1), dim3(kSumThreads), 0, s, partial, kCgBlocks, st, start ? 1 : 0);
   return hipGetLastError();
 }
 hipError_t cg_fin_cheb(const double* partial, int nblocks, double* st, bool start, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_cheb, dim3(1), dim3(kThreads), 0, s, partial, nblocks, st, start ? 1 : 0);
+  hipLaunchKernelGGL(k_fin_cheb, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st, start ? 1 : 0);
   return hipGetLastError();
 }
 hipError_t cg_cheb1(const double* r, float* z, const float* zprev, const float* dinv32, int n3, const double* st,
@@ -488,10 +460,11 @@ hipError_t cg_cheb1(const double* r, float* z, const float* zprev, const float* 
   DG_LAUNCH(k_cheb1, r, z, zprev, dinv32, n3, st, inv_theta, n, partial);
 }
 hipError_t cg_fill32(float* y, float c, long long n, hipStream_t s) { DG_LAUNCH(k_fill32, y, c, n); }
-hipError_t cg_update_p_jacobi(const double* r, double* p, const double* dinv, int n3, const double* st, long long n,
-                              hipStream_t s) {
-  DG_LAUNCH(k_update_p_jacobi, r, p, dinv, n3, st, n);
+hipError_t cg_update_p_jacobi(const double* r, double* p, double* x, const double* dinv, int n3, const double* st,
+                              long long n, hipStream_t s) {
+  DG_LAUNCH(k_update_p_jacobi, r, p, x, dinv, n3, st, n);
 }
+
 template <typename T>
 static hipError_t rprime_t(const double* r, const double* st, T* out, long long n, hipStream_t s) {
   DG_LAUNCH(k_rprime<T>, r, st, out, n);
@@ -516,17 +489,14 @@ hipError_t cg_zsums(const double* r, const float* z, const float* zprev, const d
   return zsums_t(r, z, zprev, st, n, partial, s);
 }
 template <typename T>
-static hipError_t update_p_z_t(const T* z, double* p, const double* st, long long n, hipStream_t s) {
-  DG_LAUNCH(k_update_p_z<T>, z, p, st, n);
+static hipError_t update_p_z_t(const T* z, double* p, double* x, const double* st, long long n, hipStream_t s) {
+  DG_LAUNCH(k_update_p_z<T>, z, p, x, st, n);
 }
-hipError_t cg_update_p_z(const double* z, double* p, const double* st, long long n, hipStream_t s) {
-  return update_p_z_t(z, p, st, n, s);
+hipError_t cg_update_p_z(const double* z, double* p, double* x, const double* st, long long n, hipStream_t s) {
+  return update_p_z_t(z, p, x, st, n, s);
 }
-hipError_t cg_update_p_z(const float* z, double* p, const double* st, long long n, hipStream_t s) {
-  return update_p_z_t(z, p, st, n, s);
-}
-hipError_t cg_update_p_cheb(const float* z, double* p, const double* st, long long n, hipStream_t s) {
-  DG_LAUNCH(k_update_p_cheb, z, p, st, n);
+hipError_t cg_update_p_z(const float* z, double* p, double* x, const double* st, long long n, hipStream_t s) {
+  return update_p_z_t(z, p, x, st, n, s);
 }
 
 }  // namespace dgmf

@@ -100,19 +100,19 @@ inverse_mass_kernel(const T* src, T* dst, long long nblocks, const InvMassTab<N,
 }
 
 // One step of the inverse-mass-preconditioned CG on element blocks (FP64):
-// x += alpha p and r -= alpha q (alpha from the solver state; nothing is
-// written while it is 0), z = M^-1 r, and the block sums of r.r and r.z into
-// partial[blockIdx.x] and partial[gridDim.x + blockIdx.x].  Each thread keeps
-// its updated r column in registers for r.z.
+// r -= alpha q (alpha from the solver state; r is not written while it is 0),
+// z = M^-1 r, and the block sums of r.r and r.z into partial[blockIdx.x] and
+// partial[gridDim.x + blockIdx.x].  Each thread keeps its updated r column in
+// registers for r.z.
 template <int N>
 __global__ void __launch_bounds__(LapCfgB<N>::THREADS)
-pcg_precond_kernel(double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-                   const double* __restrict__ q, double* __restrict__ z, const double* __restrict__ st,
-                   long long nblocks, const InvMassTab<N, double>* __restrict__ tab, double* __restrict__ partial) {
+pcg_precond_kernel(double* __restrict__ r, const double* __restrict__ q, double* __restrict__ z,
+                   const double* __restrict__ st, long long nblocks, const InvMassTab<N, double>* __restrict__ tab,
+                   double* __restrict__ partial) {
   using C = LapCfgB<N>;
   constexpr int N2 = N * N, N3 = N * N * N, E = C::E, ES = C::ES, PX = C::PX, PY = C::PY;
   __shared__ double U[E * ES];
-  __shared__ double red[2][C::THREADS];
+  __shared__ double red[2][(C::THREADS + 63) / 64];
   const int tid = threadIdx.x;
   const int le = tid / N2, pp = tid - le * N2;
   const int p0 = pp % N, p1 = pp / N;
@@ -129,7 +129,6 @@ pcg_precond_kernel(double* __restrict__ x, double* __restrict__ r, const double*
     if (alpha != 0.0) {
 #pragma unroll
       for (int c = 0; c < N; ++c) {
-        x[o + N2 * c] += alpha * p[o + N2 * c];
         rc[c] -= alpha * q[o + N2 * c];
         r[o + N2 * c] = rc[c];
       }
@@ -175,12 +174,26 @@ pcg_precond_kernel(double* __restrict__ x, double* __restrict__ r, const double*
       rz = fmadd(rc[c], zc, rz);
     }
   }
-  red[0][tid] = rr;
-  red[1][tid] = rz;
+  // block sums: across each wavefront (the last one may be partly filled, its
+  // missing lanes count as 0), then over the wavefronts in order.  One thread
+  // adding all of them took as long as the sweeps.
+  const int last = C::THREADS - (tid & ~63);   // lanes of this wavefront: min(64, last)
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    const double a = __shfl_down(rr, d, 64), b = __shfl_down(rz, d, 64);
+    const bool in = (tid & 63) + d < last;
+    rr += in ? a : 0.0;
+    rz += in ? b : 0.0;
+  }
+  if ((tid & 63) == 0) {
+    red[0][tid >> 6] = rr;
+    red[1][tid >> 6] = rz;
+  }
   __syncthreads();
   if (tid == 0) {
-    double a = 0, b = 0;
-    for (int i = 0; i < C::THREADS; ++i) {
+    double a = red[0][0], b = red[1][0];
+#pragma unroll
+    for (int i = 1; i < (C::THREADS + 63) / 64; ++i) {
       a += red[0][i];
       b += red[1][i];
     }
@@ -190,9 +203,8 @@ pcg_precond_kernel(double* __restrict__ x, double* __restrict__ r, const double*
 }
 
 template <int N>
-hipError_t launch_pcg_n(const std::vector<double>& Minv, double scale, long long nblocks, double* x, double* r,
-                        const double* p, const double* q, double* z, const double* st, double* partial,
-                        hipStream_t s) {
+hipError_t launch_pcg_n(const std::vector<double>& Minv, double scale, long long nblocks, double* r,
+                        const double* q, double* z, const double* st, double* partial, hipStream_t s) {
   InvMassTab<N, double> t;
   for (int i = 0; i < N; ++i)
     for (int j = 0; j < N; ++j) t.A[i][j] = Minv[i * N + j];
@@ -204,8 +216,8 @@ hipError_t launch_pcg_n(const std::vector<double>& Minv, double scale, long long
   const long long grid = (nblocks + C::E - 1) / C::E;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL((pcg_precond_kernel<N>), dim3((unsigned)grid), dim3(C::THREADS), 0, s, x, r, p, q, z, st,
-                     nblocks, dt, partial);
+  hipLaunchKernelGGL((pcg_precond_kernel<N>), dim3((unsigned)grid), dim3(C::THREADS), 0, s, r, q, z, st, nblocks,
+                     dt, partial);
   return hipGetLastError();
 }
 
@@ -362,21 +374,20 @@ long long pcg_precond_grid(int k, long long nblocks) {
   }
 }
 
-hipError_t launch_pcg_precond(int k, const std::vector<double>& Minv, double scale, long long nblocks, double* x,
-                              double* r, const double* p, const double* q, double* z, const double* st,
-                              double* partial, hipStream_t s) {
+hipError_t launch_pcg_precond(int k, const std::vector<double>& Minv, double scale, long long nblocks, double* r,
+                              const double* q, double* z, const double* st, double* partial, hipStream_t s) {
   switch (k) {
-    case 1: return launch_pcg_n<2>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 2: return launch_pcg_n<3>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 3: return launch_pcg_n<4>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 4: return launch_pcg_n<5>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 5: return launch_pcg_n<6>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 6: return launch_pcg_n<7>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 7: return launch_pcg_n<8>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 8: return launch_pcg_n<9>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 9: return launch_pcg_n<10>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 10: return launch_pcg_n<11>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
-    case 11: return launch_pcg_n<12>(Minv, scale, nblocks, x, r, p, q, z, st, partial, s);
+    case 1: return launch_pcg_n<2>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 2: return launch_pcg_n<3>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 3: return launch_pcg_n<4>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 4: return launch_pcg_n<5>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 5: return launch_pcg_n<6>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 6: return launch_pcg_n<7>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 7: return launch_pcg_n<8>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 8: return launch_pcg_n<9>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 9: return launch_pcg_n<10>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 10: return launch_pcg_n<11>(Minv, scale, nblocks, r, q, z, st, partial, s);
+    case 11: return launch_pcg_n<12>(Minv, scale, nblocks, r, q, z, st, partial, s);
     default: return hipErrorInvalidValue;
   }
 }

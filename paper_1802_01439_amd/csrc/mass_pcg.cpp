@@ -179,10 +179,10 @@ int dgmf::mass_pcg_solve(const dg_op_desc* desc, int32_t op, double mass_factor,
       for (int i = 0; i < batch; ++i) {
         MPCG_CHECK(apply_dot(w.p, w.q, w.partial), "operator launch");
         MPCG_CHECK(cg_fin_alpha(w.partial, (int)qgrid, w.st, s), "alpha");
-        MPCG_CHECK(launch_pcg_precond(desc->degree, Minv, ivol, nblocks, x, w.r, w.p, w.q, w.z, w.st, w.partial, s),
-                   "update and inverse mass");
-        MPCG_CHECK(mpcg_beta(w.partial, w.partial + pgrid, (int)pgrid, w.st, s), "beta");
-        MPCG_CHECK(mpcg_xpby(w.p, w.z, w.st, n, s), "direction update");
+        MPCG_CHECK(launch_pcg_precond(desc->degree, Minv, ivol, nblocks, w.r, w.q, w.z, w.st, w.partial, s),
+                   "residual update and inverse mass");
+        MPCG_CHECK(mpcg_beta(w.partial, (int)pgrid, w.st, s), "beta");
+        MPCG_CHECK(mpcg_update_xp(x, w.p, w.z, w.st, n, s), "direction update");
       }
       matvec += batch;
       launched += batch;

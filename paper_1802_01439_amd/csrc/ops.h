@@ -103,12 +103,11 @@ struct DivPlan {
 };
 
 hipError_t launch_divergence(const DivPlan& P, bool f32, const void* u, void* b, hipStream_t s);
-// inverse-mass-preconditioned CG step on element blocks (FP64): x += alpha p,
+// inverse-mass-preconditioned CG step on element blocks (FP64):
 // r -= alpha q, z = M^-1 r, block sums of r.r and r.z (2 * grid doubles)
 long long pcg_precond_grid(int k, long long nblocks);
-hipError_t launch_pcg_precond(int k, const std::vector<double>& Minv, double scale, long long nblocks, double* x,
-                              double* r, const double* p, const double* q, double* z, const double* st,
-                              double* partial, hipStream_t s);
+hipError_t launch_pcg_precond(int k, const std::vector<double>& Minv, double scale, long long nblocks, double* r,
+                              const double* q, double* z, const double* st, double* partial, hipStream_t s);
 // h-multigrid level transfers between a mesh (coarse) and the mesh with every
 // element split in two per direction: P[c] = child_interp(k, c)
 struct TransferPlan {

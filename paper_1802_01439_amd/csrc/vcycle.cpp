@@ -354,7 +354,7 @@ int gmg_cg(const dg_op_desc* desc, int32_t levels, int degree, double smoothing_
     if ((er = M.cycle(0)) != hipSuccess) return er;
     if ((er = cg_zsums(r, zb[zn], zb[1 - zn], st, n, partial, s)) != hipSuccess) return er;
     if ((er = cg_fin_cheb(partial, kCgBlocks, st, start, s)) != hipSuccess) return er;
-    if ((er = cg_update_p_z(zb[zn], p, st, n, s)) != hipSuccess) return er;
+    if ((er = cg_update_p_z(zb[zn], p, x, st, n, s)) != hipSuccess) return er;
     zn = 1 - zn;
     return hipSuccess;
   };
@@ -367,7 +367,7 @@ int gmg_cg(const dg_op_desc* desc, int32_t levels, int degree, double smoothing_
       GMG_CHECK(cg_fill(zb[1], 0.0, n, s), "fill");
     }
     // start: alpha is 0 in the fresh state, so this only forms the sums of r0
-    GMG_CHECK(cg_update_xr_st(x, r, p, q, nullptr, M.n3, st, false, n, partial, s), "update");
+    GMG_CHECK(cg_update_r_st(r, q, nullptr, M.n3, st, false, n, partial, s), "update");
     GMG_CHECK(precondition(true), "V-cycle");
     // batch size: up to 4, fewer when the observed contraction rate says the
     // tolerance is that close (keeps queued no-op iterations rare)
@@ -387,11 +387,12 @@ int gmg_cg(const dg_op_desc* desc, int32_t levels, int degree, double smoothing_
       rn2_prev = host[kRN2];
       it_prev = host[kIter];
       for (int b2 = 0; b2 < batch; ++b2) {
-        // q = A p with the p.q partials, alpha, x/r update with the sums of r
+        // q = A p with the p.q partials, alpha, r update with the sums of r;
+        // the direction update after the cycle moves x
         ++matvec;
         GMG_CHECK(cg_apply_dot(A, p, q, partial, s), "operator launch");
         GMG_CHECK(cg_fin_alpha(partial, (int)grid64, st, s), "alpha");
-        GMG_CHECK(cg_update_xr_st(x, r, p, q, nullptr, M.n3, st, false, n, partial, s), "update");
+        GMG_CHECK(cg_update_r_st(r, q, nullptr, M.n3, st, false, n, partial, s), "update");
         GMG_CHECK(precondition(false), "V-cycle");
       }
       queued += batch;
