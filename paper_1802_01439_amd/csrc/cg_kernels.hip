@@ -213,19 +213,6 @@ __global__ void __launch_bounds__(kThreads) k_update_r_st(double* __restrict__ r
   block_partials<JAC ? 4 : 2>(v, partial);
 }
 
-// x += alpha p, then p = z + beta p, of entry i (z formed by the caller): a
-// zero alpha touches no x, a zero beta never reads the old direction for p
-__device__ __forceinline__ void step_xp(double* __restrict__ x, double* __restrict__ p, long long i, double alpha,
-                                        double beta, double zi) {
-  if (alpha != 0.0 || beta != 0.0) {
-    const double pi = p[i];
-    if (alpha != 0.0) x[i] += alpha * pi;
-    p[i] = beta != 0.0 ? zi + beta * pi : zi;
-  } else {
-    p[i] = zi;
-  }
-}
-
 // count the iteration (not for the start) and test convergence / limits
 __device__ void account(double* st, double rn2, double rz, bool start) {
   if (!start) st[kIter] += 1.0;
@@ -286,8 +273,11 @@ __global__ void __launch_bounds__(kThreads) k_update_p_jacobi(const double* __re
                                                               double* __restrict__ x, const double* __restrict__ dinv,
                                                               int n3, const double* __restrict__ st, long long n) {
   const double alpha = st[kAlpha], mu = st[kMuR], muz = st[kMuZ], beta = st[kBeta];
-  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads)
-    step_xp(x, p, i, alpha, beta, fma(dinv[i % n3], r[i] - mu, -muz));
+  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
+    const double zi = fma(dinv[i % n3], r[i] - mu, -muz), pi = p[i];
+    if (alpha != 0.0) x[i] += alpha * pi;
+    p[i] = beta != 0.0 ? zi + beta * pi : zi;   // a zero beta never uses the old direction
+  }
 }
 
 // Chebyshev degree 1 (no operator apply): z = D^-1 r' / theta and the
@@ -363,13 +353,11 @@ __global__ void __launch_bounds__(kThreads) k_zsums(const double* __restrict__ r
   block_partials<3>(v, partial);
 }
 
-template <typename T>
+template <typename T, int R>
 __global__ void __launch_bounds__(kThreads) k_update_p_z(const T* __restrict__ z, double* __restrict__ p,
                                                          double* __restrict__ x, const double* __restrict__ st,
                                                          long long n) {
-  const double alpha = st[kAlpha], muz = st[kMuZ], beta = st[kBeta];
-  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads)
-    step_xp(x, p, i, alpha, beta, (double)z[i] - muz);
+  step_xp<R>(x, p, z, st[kAlpha], st[kBeta], st[kMuZ], n);
 }
 
 // state set-up: zero, then the constants
@@ -490,7 +478,8 @@ hipError_t cg_zsums(const double* r, const float* z, const float* zprev, const d
 }
 template <typename T>
 static hipError_t update_p_z_t(const T* z, double* p, double* x, const double* st, long long n, hipStream_t s) {
-  DG_LAUNCH(k_update_p_z<T>, z, p, x, st, n);
+  if (xp_in_cache(n)) DG_LAUNCH((k_update_p_z<T, 2>), z, p, x, st, n);
+  DG_LAUNCH((k_update_p_z<T, 1>), z, p, x, st, n);
 }
 hipError_t cg_update_p_z(const double* z, double* p, double* x, const double* st, long long n, hipStream_t s) {
   return update_p_z_t(z, p, x, st, n, s);

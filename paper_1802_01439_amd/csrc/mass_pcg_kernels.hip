@@ -60,24 +60,14 @@ __global__ void __launch_bounds__(kSumThreads) k_mp_beta(const double* __restric
   st[kRZ] = rz;
 }
 
-// x += alpha p, then p = z + beta p (scalars from the state; a zero alpha
-// touches no x, a zero beta never reads the old direction for p).  x moves here
-// and not with r, because p is read here anyway: 4 + 5 vectors per iteration
-// in the two kernels instead of 7 + 3.
+// x += alpha p, then p = z + beta p (scalars from the state).  x moves here and
+// not with r, because p is read here anyway: 4 + 5 vectors per iteration in
+// the two kernels instead of 7 + 3.
+template <int R>
 __global__ void __launch_bounds__(kThreads) k_mp_update_xp(double* __restrict__ x, double* __restrict__ p,
                                                            const double* __restrict__ z,
                                                            const double* __restrict__ st, long long n) {
-  const double alpha = st[kAlpha], beta = st[kBeta];
-  for (long long i = blockIdx.x * (long long)kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
-    const double zi = z[i];
-    if (alpha != 0.0 || beta != 0.0) {
-      const double pi = p[i];
-      if (alpha != 0.0) x[i] += alpha * pi;
-      p[i] = beta != 0.0 ? zi + beta * pi : zi;
-    } else {
-      p[i] = zi;
-    }
-  }
+  step_xp<R>(x, p, z, st[kAlpha], st[kBeta], 0.0, n);
 }
 
 }  // namespace
@@ -93,7 +83,8 @@ hipError_t mpcg_beta(const double* partial, int nblocks, double* st, hipStream_t
 }
 
 hipError_t mpcg_update_xp(double* x, double* p, const double* z, const double* st, long long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_mp_update_xp, dim3(kCgBlocks), dim3(kThreads), 0, s, x, p, z, st, n);
+  hipLaunchKernelGGL(xp_in_cache(n) ? k_mp_update_xp<2> : k_mp_update_xp<1>, dim3(kCgBlocks), dim3(kThreads), 0, s, x,
+                     p, z, st, n);
   return hipGetLastError();
 }
 
