@@ -22,7 +22,8 @@
 // by three M sweeps: six 1D sweeps per element instead of the eight of the
 // unfactored form.
 //
-// GPU mapping, FP64 n <= 5 and FP32 n = 3, 5.  A workgroup owns an x-y tile
+// GPU mapping, FP64 n <= 5 and FP32 n = 3, 5 on large meshes (see lap_march).
+// A workgroup owns an x-y tile
 // of TX x TY elements (n^2 threads per element) and marches through a segment
 // of consecutive z layers.  Every element column is loaded from global memory
 // once, one layer ahead: when a thread reaches layer ez it already holds its
@@ -33,9 +34,8 @@
 // column in registers), Y (Ly), X (Lx then Mx), Y (My), Z (Mz, written once),
 // with pencils handed over through two LDS buffers (4 barriers).
 //
-// GPU mapping, n >= 6 and FP32 n = 2, 4 (measured: there the march's serial
-// layer steps and register pressure cost more than the neighbour loads it
-// saves): one workgroup per batch of E = floor(256/n^2) consecutive
+// GPU mapping otherwise (measured: there the march's serial layer steps and
+// register pressure cost more than the neighbour loads it saves): one workgroup per batch of E = floor(256/n^2) consecutive
 // elements, batches walked strip by strip, XCD by XCD; each thread first
 // issues all of its global loads (own z column and the neighbour pencils,
 // reduced at once to end values and slopes), then the same five phases.  What
@@ -851,28 +851,44 @@ const LapTab<N, T>* lap_device_tab(const LaplacePlan& P, hipError_t* err) {
   return device_table_of("laplace", make_lap_tab<N, T>(P), err);
 }
 
-// measured choice: the march wins for FP64 up to n = 5 and for FP32 at
-// n = 3 and 5; the batch kernel is faster everywhere else
+// The march kernel is built for FP64 up to n = 5 and for FP32 at n = 3 and 5
+// (the batch kernel is faster at every size elsewhere), and taken where input
+// and output together exceed 96 MB.  Below, the batch kernel's second reads of
+// neighbour pencils come from the caches, and its many short workgroups fill
+// the device better than few long marches; above, they come from memory, and
+// the march reads every column once.  Batch against march, us (bit-identical):
+// FP64 n = 5, 32^3 (66 MB) 20.1 / 24.6, 36^3 (93) 30.1 / 35.1, 40^3 (128)
+// 47.6 / 46.0, 51^3 (265) 98.3 / 94.1; n = 4, 44^3 (87) 24.0 / 27.2, 64^3 (268)
+// 81.9 / 71.6; n = 3, 48^3 (48) 15.6 / 16.7, 90^3 (315) 120 / 105; FP32 n = 5,
+// 40^3 (64) 24.6 / 26.9, 51^3 (133) 60.3 / 56.8; n = 3, 90^3 (157) 77.8 / 72.2.
 template <int N, typename T>
-constexpr bool lap_march() {
+constexpr bool lap_has_march() {
   return sizeof(T) == 8 ? N <= 5 : (N == 3 || N == 5);
+}
+
+// Planes that hold less than one full batch stay with the march: their batches
+// would be mostly empty, and a reduction's partials (one per workgroup) many.
+template <int N, typename T>
+bool lap_march(const LaplacePlan& P) {
+  if constexpr (!lap_has_march<N, T>()) return false;
+  return (long long)P.n_comp * P.mesh.n_el * (N * N * N) * 2 * (long long)sizeof(T) > 96LL << 20 ||
+         (long long)P.mesh.nx * P.mesh.ny < LapCfgB<N>::E;
 }
 
 // Workgroups of one launch (for the size of a partial-sum buffer).
 template <int N, typename T>
 long lap_grid(const LaplacePlan& P) {
-  if constexpr (!lap_march<N, T>()) {
+  if (!lap_march<N, T>(P)) {
     using CB = LapCfgB<N>;
     const long PB = (P.mesh.nx * (long)P.mesh.ny + CB::E - 1) / CB::E;
     return PB * P.n_comp * P.mesh.nz;
-  } else {
-    using C = LapCfg<N>;
-    const long ntx = (P.mesh.nx + C::TX - 1) / C::TX, nty = (P.mesh.ny + C::TY - 1) / C::TY;
-    const long tiles = ntx * nty * P.n_comp;
-    const long want = std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
-    const long lz = (P.mesh.nz + want - 1) / want;
-    return tiles * ((P.mesh.nz + lz - 1) / lz);
   }
+  using C = LapCfg<N>;
+  const long ntx = (P.mesh.nx + C::TX - 1) / C::TX, nty = (P.mesh.ny + C::TY - 1) / C::TY;
+  const long tiles = ntx * nty * P.n_comp;
+  const long want = std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
+  const long lz = (P.mesh.nz + want - 1) / want;
+  return tiles * ((P.mesh.nz + lz - 1) / lz);
 }
 
 // Launch y = A x through io.  tab: device table from lap_device_tab, or
@@ -884,31 +900,33 @@ hipError_t launch_laplace_io(const LaplacePlan& P, const IO& io, const LapTab<N,
     tab = plan_table<LapTab<N, T>>(P.tab.p[sizeof(T) == 4], "laplace", [&] { return make_lap_tab<N, T>(P); }, &err);
     if (!tab) return err;
   }
-  if constexpr (!lap_march<N, T>()) {
-    using CB = LapCfgB<N>;
-    Traversal tv;
-    tv.PB = (P.mesh.nx * P.mesh.ny + CB::E - 1) / CB::E;
-    tv.PZ = P.n_comp * P.mesh.nz;
-    tv.S = std::max(1, std::min(tv.PB, (lap_strip_rows<N>() * P.mesh.nx + CB::E / 2) / CB::E));
-    const long grid = (long)tv.PB * tv.PZ;
-    if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((laplace_batch_kernel<N, T, IO>), dim3((unsigned)grid), dim3(CB::THREADS), 0, stream, io,
-                       P.mesh, tv, tab);
-  } else {
-    // tiles x z segments x components, about kLapMarchWGs workgroups
-    using C = LapCfg<N>;
-    LapWork wk;
-    wk.ntx = (P.mesh.nx + C::TX - 1) / C::TX;
-    wk.nty = (P.mesh.ny + C::TY - 1) / C::TY;
-    const long tiles = (long)wk.ntx * wk.nty * P.n_comp;
-    const int want = (int)std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
-    wk.lz = (P.mesh.nz + want - 1) / want;
-    wk.nseg = (P.mesh.nz + wk.lz - 1) / wk.lz;
-    const long grid = tiles * wk.nseg;
-    if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((laplace_march_kernel<N, T, IO>), dim3((unsigned)grid), dim3(C::THREADS), 0, stream, io,
-                       P.mesh, wk, tab);
+  if constexpr (lap_has_march<N, T>()) {
+    if (lap_march<N, T>(P)) {
+      // tiles x z segments x components, about kLapMarchWGs workgroups
+      using C = LapCfg<N>;
+      LapWork wk;
+      wk.ntx = (P.mesh.nx + C::TX - 1) / C::TX;
+      wk.nty = (P.mesh.ny + C::TY - 1) / C::TY;
+      const long tiles = (long)wk.ntx * wk.nty * P.n_comp;
+      const int want = (int)std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
+      wk.lz = (P.mesh.nz + want - 1) / want;
+      wk.nseg = (P.mesh.nz + wk.lz - 1) / wk.lz;
+      const long grid = tiles * wk.nseg;
+      if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
+      hipLaunchKernelGGL((laplace_march_kernel<N, T, IO>), dim3((unsigned)grid), dim3(C::THREADS), 0, stream, io,
+                         P.mesh, wk, tab);
+      return hipGetLastError();
+    }
   }
+  using CB = LapCfgB<N>;
+  Traversal tv;
+  tv.PB = (P.mesh.nx * P.mesh.ny + CB::E - 1) / CB::E;
+  tv.PZ = P.n_comp * P.mesh.nz;
+  tv.S = std::max(1, std::min(tv.PB, (lap_strip_rows<N>() * P.mesh.nx + CB::E / 2) / CB::E));
+  const long grid = (long)tv.PB * tv.PZ;
+  if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL((laplace_batch_kernel<N, T, IO>), dim3((unsigned)grid), dim3(CB::THREADS), 0, stream, io,
+                     P.mesh, tv, tab);
   return hipGetLastError();
 }
 

@@ -178,3 +178,38 @@ def test_three_components_low_degree():
     y = _run(k, n_el, msh.length, u, penalty_factor=1.5, scale=0.25)
     ref = laplace_apply(u, k, msh, penalty_factor=1.5, scale=0.25)
     assert rel_err(y, ref) < 1e-12
+
+
+@pytest.mark.parametrize("k,n_el,n_comp,dtype", [
+    (1, (93, 92, 93), 1, torch.float64), (2, (62, 63, 61), 1, torch.float64), (4, (21, 25, 33), 3, torch.float64),
+    (2, (78, 77, 79), 1, torch.float32), (4, (47, 46, 48), 1, torch.float32),
+    (1, (91, 92, 93), 1, torch.float64), (4, (36, 37, 37), 1, torch.float64)])
+def test_low_degrees_on_both_sides_of_the_march(k, n_el, n_comp, dtype):
+    """Input and output just above 96 MB (the marching kernel) and, the last
+    two, just below (the batch kernel); sampled elements with the wrap-around."""
+    msh = M.Mesh(n_el, (2.0, 1.7, 2.3))
+    u = inputs.uniform((n_comp, msh.N, (k + 1) ** 3), seed=430 + k)
+    if dtype == torch.float32:
+        u = round_f32(u)
+    announce(f"laplace march rule k={k} {dtype} n_el={n_el} n_comp={n_comp}")
+    y = _run(k, n_el, msh.length, u if n_comp == 3 else u[0], dtype=dtype)
+    y = y if n_comp == 3 else y[None]
+    rng = np.random.default_rng(13)
+    nx, ny, _ = n_el
+    sample = np.unique(np.concatenate([rng.integers(0, msh.N, 150), [0, nx - 1, nx, nx * ny - 1, nx * ny, msh.N - 1]]))
+    tol = 1e-12 if dtype == torch.float64 else 1e-5
+    for c in range(n_comp):
+        assert rel_err(y[c][sample], laplace_apply(u[c], k, msh, elems=sample)) < tol
+
+
+@pytest.mark.parametrize("n_el", [(37, 38, 37), (35, 36, 37)])
+def test_cg_partial_sums_on_both_sides_of_the_march(n_el):
+    """p.Ap from the workgroups of either kernel: after a few CG steps the
+    recurrence's residual is the true one."""
+    d = dgmf.make_desc(4, n_el, (2.0, 1.7, 2.3))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    b = 2 * torch.rand(n_el[0] * n_el[1] * n_el[2], 125, device="cuda", dtype=torch.float64, generator=g) - 1
+    announce(f"CG at the march rule n_el={n_el}")
+    _, rep, rc = dgmf.cg_solve(d, b, rtol=1e-12, max_iter=6)
+    assert rc == dgmf.DG_NOT_CONVERGED and rep["iterations"] == 6
+    assert abs(rep["true_rel_res"] - rep["rel_res"]) < 1e-10 * rep["rel_res"]
