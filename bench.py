@@ -47,11 +47,12 @@ SUMMARY_MAX_CHARS = 4096
 BYTES_PER_DOF = {("laplace", "f64"): 16, ("laplace", "f32"): 8,
                  ("convective", "f64"): 16, ("convective", "f32"): 8,
                  ("vjp", "f64"): 24, ("vjp", "f32"): 12}
-KERNEL_NAME = {"laplace": "laplace_march_kernel|laplace_batch_kernel", "convective": "convective_kernel", "vjp": "convective_vjp_kernel"}
+KERNEL_NAME = {"laplace": "laplace_march_kernel|laplace_batch_kernel", "convective": "convective_kernel|convective_split_kernel",
+               "vjp": "vjp_onepass_kernel|vjp_split_kernel"}
 # every source file that defines each kernel (the traffic record is keyed by their hash)
 SOURCES = {"laplace": ("laplace.hip", "laplace_kernels.h", "common.h"),
-           "convective": ("convective.hip", "conv_common.h", "basis_ct.h", "common.h"),
-           "vjp": ("convective_vjp.hip", "conv_common.h", "basis_ct.h", "common.h")}
+           "convective": ("convective.hip", "convective_split.hip", "conv_common.h", "basis_ct.h", "common.h"),
+           "vjp": ("convective_vjp.hip", "convective_vjp_split.hip", "conv_common.h", "basis_ct.h", "common.h")}
 
 
 def sweep_mesh(k):
