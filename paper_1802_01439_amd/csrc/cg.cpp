@@ -8,7 +8,7 @@
 // performs its Chebyshev step in the epilogue (the first one forms its
 // operand from the FP64 residual, the last one sums what the flexible beta
 // needs).  Per iteration: FP64 apply with the p.Ap
-// sums, x/r update, the FP32 applies, p update, and one-workgroup kernels
+// sums, r update, the FP32 applies, x and p update, and one-workgroup kernels
 // finishing the sums.
 //
 // Variant: flexible (Polak-Ribiere) CG, beta = r+.(z+ - z)/(r.z), so that a

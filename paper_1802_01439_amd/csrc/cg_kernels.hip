@@ -227,7 +227,7 @@ __device__ void account(double* st, double rn2, double rz, bool start) {
   }
 }
 
-// Jacobi: scalars of the new residual (sums from k_update_xr_st<true>);
+// Jacobi: scalars of the new residual (sums from k_update_r_st<true>);
 // beta = rz_new / rz (a fixed symmetric preconditioner: standard PCG)
 __global__ void __launch_bounds__(kSumThreads) k_fin_jacobi(const double* __restrict__ partial, int nblocks,
                                                          double* __restrict__ st, int start) {
@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(kSumThreads) k_fin_jacobi(const double* __rest
 }
 
 
-// Chebyshev: mean and norm of the new residual (sums from k_update_xr_st<false>)
+// Chebyshev: mean and norm of the new residual (sums from k_update_r_st<false>)
 __global__ void __launch_bounds__(kSumThreads) k_fin_resid(const double* __restrict__ partial, int nblocks,
                                                         double* __restrict__ st, int start) {
   double v[2];

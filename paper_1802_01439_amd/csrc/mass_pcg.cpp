@@ -5,9 +5,9 @@
 //
 // Per iteration: q = A p (projection or Helmholtz kernel, with the partial
 // sums of p.q in its epilogue) and alpha;
-// one fused kernel for x += alpha p, r -= alpha q, z = M^-1 r and the sums
-// r.r, r.z (56 B/DoF instead of 80 for the three separate passes); the
-// convergence test and beta; p = z + beta p.
+// one fused kernel for r -= alpha q, z = M^-1 r and the sums
+// r.r, r.z (32 B/DoF); the convergence test and beta; x += alpha p and
+// p = z + beta p in one pass (40 B/DoF).
 // The scalars stay on the device; the host reads the state once per batch of
 // iterations, sized from the observed contraction rate.  Once converged, the
 // remaining iterations of a batch change nothing (alpha = 0).

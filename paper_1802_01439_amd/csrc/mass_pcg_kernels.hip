@@ -1,7 +1,7 @@
 // Scalar steps of the inverse-mass-preconditioned CG with its scalars kept on
 // the device (the state array of the CG solver: kRZ, kBeta, kRN2, kDone,
 // kStatus, kIter, kTol2, kMaxIt), so that iterations run in batches between
-// host reads.  p.Ap and alpha come from the CG kernels, the x/r update with
+// host reads.  p.Ap and alpha come from the CG kernels, the r update with
 // z = M^-1 r and the sums r.r, r.z from the fused inverse mass kernel.
 #include "cg_kernels.h"
 #include "cg_sums.h"
