@@ -102,7 +102,6 @@ convective_kernel(const T* __restrict__ u, T* __restrict__ r, MeshArgs mesh,
   constexpr int FXo = FYo + Sh::FL;
   constexpr int XRo = FXo + Sh::FL;
   __shared__ T lds[E * PER];
-  const int tid = threadIdx.x;
   const size_t cs = (size_t)mesh.n_el * N3;
   const int nxy = mesh.nx * mesh.ny;
   // this workgroup's E consecutive elements: first element, element count
@@ -189,8 +188,11 @@ convective_kernel(const T* __restrict__ u, T* __restrict__ r, MeshArgs mesh,
   int d1[NI1], ds[NI1], d2[NI1];
   // issue every load of this thread's items (written as a lambda with nested
   // conditions: as a plain loop with continue the compiler's code was 1-2.5 %
-  // slower at FP32 k = 1, 2 and FP64 k = 1)
+  // slower at FP32 k = 1, 2 and FP64 k = 1; with one thread index for it and
+  // the phases below, and the back sweeps as plain blocks, FP64 k = 3 took 4
+  // registers less and 0.7 % longer: 40^3 141.2 us, as written here 140.5)
   auto issue = [&]() {
+    const int tid = threadIdx.x;
 #pragma unroll
     for (int i = 0; i < NI1; ++i) {
       const int w = tid + i * TH;
@@ -217,6 +219,7 @@ convective_kernel(const T* __restrict__ u, T* __restrict__ r, MeshArgs mesh,
     }
   };
   issue();
+  const int tid = threadIdx.x;
 #pragma unroll
   for (int i = 0; i < NI1; ++i) {
     if (d1[i] >= 0) {
@@ -418,7 +421,7 @@ convective_kernel(const T* __restrict__ u, T* __restrict__ r, MeshArgs mesh,
   __syncthreads();
 
   // ---------------- Y and X back sweeps ----------------
-  {
+  auto back_y = [&]() {
     constexpr int nYc = 3 * E * N * Q, nXf = 3 * E * 2 * N;
     constexpr int FX = wave_split(nYc, nXf, TH);   // first x-face item
     for (int w = tid; w < FX + nXf; w += TH) {
@@ -477,9 +480,8 @@ convective_kernel(const T* __restrict__ u, T* __restrict__ r, MeshArgs mesh,
         for (int b = 0; b < N; ++b) xr[b] = o.out(b);
       }
     }
-  }
-  __syncthreads();
-  {
+  };
+  auto back_x = [&]() {
     constexpr int nXc = 3 * E * N2;
     for (int w = tid; w < nXc; w += TH) {
       CONV_TABLES(t);
@@ -515,7 +517,10 @@ convective_kernel(const T* __restrict__ u, T* __restrict__ r, MeshArgs mesh,
         g[a] = o;
       }
     }
-  }
+  };
+  back_y();
+  __syncthreads();
+  back_x();
 }
 
 template <int N, int Q, typename T>
