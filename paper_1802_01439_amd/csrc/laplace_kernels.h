@@ -46,7 +46,9 @@
 // are therefore read from LDS in the X phase; only pencils across a batch or
 // row end come from memory.  Degree-sweep meshes, us: FP64 k = 5 109 -> 98,
 // 6 118 -> 105, 7 95 -> 86, 8 101 -> 97; FP32 k = 6 69 -> 64, 7 51 -> 43,
-// 10 56 -> 53 (bit-identical); 384 or 512 threads: 0-70 % slower.
+// 10 56 -> 53 (bit-identical); 384 or 512 threads: 0-70 % slower.  Where that
+// does not pay (n = 2, and n = 4, 8, 10 on meshes that stay in the caches) all
+// neighbours are loaded: see lap_x_lds.
 //
 // The 1D tables are a small device table read through the scalar unit.  No
 // atomics.
@@ -65,6 +67,7 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "api_internal.h"
 #include "common.h"
@@ -336,7 +339,8 @@ struct Pencils {
   T xl[N], xr[N];    // x-neighbours, x-pencil (b,c) = (p0,p1)
 };
 
-template <int N, typename T, typename IO>
+// XL: x-neighbours of the same batch (inL, inR) are left to the X phase.
+template <int N, typename T, bool XL, typename IO>
 __device__ __forceinline__ void load_pencils(const IO& io, const MeshArgs& mesh, const BatchPos& b, int p0, int p1,
                                              bool inL, bool inR, Pencils<N, T>& P) {
   constexpr int N2 = N * N, N3 = N * N * N;
@@ -358,7 +362,12 @@ __device__ __forceinline__ void load_pencils(const IO& io, const MeshArgs& mesh,
     P.zr[c] = io.load(zr + N2 * c, lz + N2 * c);
     P.yl[c] = io.load(yl + N * c, ly + N * c);
     P.yr[c] = io.load(yr + N * c, ly + N * c);
+    if constexpr (!XL) {
+      P.xl[c] = io.load(xl + c, lx + c);
+      P.xr[c] = io.load(xr + c, lx + c);
+    }
   }
+  if constexpr (!XL) return;
   // x pencils of neighbours outside the batch: a wavefront reads up to 64 cache
   // lines with each load instruction
   if (!inL) {
@@ -381,13 +390,17 @@ struct BatchIn {
   NbrFace<T> fx, fy, fz;
 };
 
-template <int N, typename T>
+template <int N, typename T, bool XL>
 __device__ __forceinline__ void reduce_pencils(const LapTab<N, T>& t, const Pencils<N, T>& P, bool inL, bool inR,
                                                BatchIn<N, T>& I) {
 #pragma unroll
   for (int c = 0; c < N; ++c) I.own[c] = P.own[c];
   I.fz = nbr_face<N, T>(t, P.zl, P.zr);
   I.fy = nbr_face<N, T>(t, P.yl, P.yr);
+  if constexpr (!XL) {
+    I.fx = nbr_face<N, T>(t, P.xl, P.xr);
+    return;
+  }
   I.fx.vL = I.fx.gL = I.fx.vR = I.fx.gR = T(0);
   if (!inL) {
     T g = 0;
@@ -489,7 +502,7 @@ __device__ __forceinline__ void laplace_batch(const LapTab<N, T>& t, const Batch
 // Batch kernel: one workgroup per batch, batches in traversal order (XCD by XCD).  All
 // global loads of the batch are issued first and reduced to the own column
 // plus the neighbours' end values and slopes; then the five phases run.
-template <int N, typename T, typename IO>
+template <int N, typename T, typename IO, bool XL>
 __global__ void __launch_bounds__(LapCfgB<N>::THREADS)
 laplace_batch_kernel(IO io, MeshArgs mesh, Traversal tv, const LapTab<N, T>* __restrict__ tab) {
   const LapTab<N, T>& t = *tab;
@@ -504,12 +517,13 @@ laplace_batch_kernel(IO io, MeshArgs mesh, Traversal tv, const LapTab<N, T>* __r
   const int le = tid / N2, p = tid - le * N2;
   const int p0 = p % N, p1 = p / N;
   const BatchPos b = batch_pos(xcd_remap(blockIdx.x, gridDim.x), tv, mesh, E, le);
-  const bool inL = E > 1 && le > 0 && b.ex > 0, inR = E > 1 && le + 1 < b.ne && b.ex + 1 < mesh.nx;
+  static_assert(!XL || E > 1, "a batch of one element has no neighbour in it");
+  const bool inL = XL && le > 0 && b.ex > 0, inR = XL && le + 1 < b.ne && b.ex + 1 < mesh.nx;
   BatchIn<N, T> I;
   if (b.active) {
     Pencils<N, T> P;
-    load_pencils<N, T>(io, mesh, b, p0, p1, inL, inR, P);
-    reduce_pencils<N, T>(t, P, inL, inR, I);
+    load_pencils<N, T, XL>(io, mesh, b, p0, p1, inL, inR, P);
+    reduce_pencils<N, T, XL>(t, P, inL, inR, I);
   }
   laplace_batch<N, T>(t, b, I, inL, inR, io, U + le * ES, V + le * ES, p0, p1);
   io.template finish<C::THREADS, sizeof(UV)>(UV);
@@ -866,12 +880,47 @@ constexpr bool lap_has_march() {
   return sizeof(T) == 8 ? N <= 5 : (N == 3 || N == 5);
 }
 
+// Input and output of one launch, bytes.
+template <int N, typename T>
+long long lap_bytes(const LaplacePlan& P) {
+  return (long long)P.n_comp * P.mesh.n_el * (N * N * N) * 2 * (long long)sizeof(T);
+}
+
+// Whether the batch kernel takes x-neighbours of the same batch from LDS.  From
+// memory that saves requests and traffic (FP32 n = 8, 33x24x41, 127 MB: 43.0
+// against 50.3 us; n = 4, 152 MB 54.5 / 57.4; FP64 n = 10, 254 MB 113.8 /
+// 117.2).  While input and output stay in the caches it only moves loads into
+// the X phase, after the barrier: most degrees still gain 0-4 %, but FP32
+// n = 4 loses up to 5 % (47 MB 15.6 / 14.8), n = 8 3-5 % (75 MB 23.4 / 22.3;
+// 21 MB 10.3 / 10.4), FP64 n = 10, with two elements a batch, 3-8 % (64 MB
+// 32.5 / 30.0; 16 MB 13.0 / 13.7, 136 MB 62.3 / 62.8).  n = 2, whose pencil is
+// one 8-byte load, loses 2 % at every size.  The forms with a fused epilogue
+// move more vectors an entry: at n = 8 they are 0-0.3 % faster with LDS (a
+// V-cycle CG solve, 24^3, 10.04 / 10.07 ms), at n = 4 and 10 as the plain one
+// (40^3, n = 4 4.92 / 4.84 ms).  (The same bits either way.)
+template <int N, typename T, typename IO>
+constexpr bool lap_x_by_size() {
+  if (sizeof(T) == 8) return N == 10;
+  return N == 4 || (N == 8 && std::is_same<IO, LapPlainIO<T>>::value);
+}
+template <int N, typename T>
+constexpr bool lap_x_ever_lds() {
+  return LapCfgB<N>::E > 1 && !(N == 2 && sizeof(T) == 4);
+}
+template <int N, typename T, typename IO>
+bool lap_x_lds(const LaplacePlan& P) {
+  if constexpr (!lap_x_by_size<N, T, IO>()) return lap_x_ever_lds<N, T>();
+  constexpr long long lo = N == 4 ? 0 : 24LL << 20, hi = (N == 10 ? 120LL : 88LL) << 20;
+  const long long b = lap_bytes<N, T>(P);
+  return b <= lo || b > hi;
+}
+
 // Planes that hold less than one full batch stay with the march: their batches
 // would be mostly empty, and a reduction's partials (one per workgroup) many.
 template <int N, typename T>
 bool lap_march(const LaplacePlan& P) {
   if constexpr (!lap_has_march<N, T>()) return false;
-  return (long long)P.n_comp * P.mesh.n_el * (N * N * N) * 2 * (long long)sizeof(T) > 96LL << 20 ||
+  return lap_bytes<N, T>(P) > 96LL << 20 ||
          (long long)P.mesh.nx * P.mesh.ny < LapCfgB<N>::E;
 }
 
@@ -925,8 +974,16 @@ hipError_t launch_laplace_io(const LaplacePlan& P, const IO& io, const LapTab<N,
   tv.S = std::max(1, std::min(tv.PB, (lap_strip_rows<N>() * P.mesh.nx + CB::E / 2) / CB::E));
   const long grid = (long)tv.PB * tv.PZ;
   if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((laplace_batch_kernel<N, T, IO>), dim3((unsigned)grid), dim3(CB::THREADS), 0, stream, io,
-                     P.mesh, tv, tab);
+  if constexpr (lap_x_ever_lds<N, T>()) {
+    if (lap_x_lds<N, T, IO>(P)) {
+      hipLaunchKernelGGL((laplace_batch_kernel<N, T, IO, true>), dim3((unsigned)grid), dim3(CB::THREADS), 0, stream,
+                         io, P.mesh, tv, tab);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (lap_x_by_size<N, T, IO>() || !lap_x_ever_lds<N, T>())
+    hipLaunchKernelGGL((laplace_batch_kernel<N, T, IO, false>), dim3((unsigned)grid), dim3(CB::THREADS), 0, stream, io,
+                       P.mesh, tv, tab);
   return hipGetLastError();
 }
 

@@ -213,3 +213,28 @@ def test_cg_partial_sums_on_both_sides_of_the_march(n_el):
     _, rep, rc = dgmf.cg_solve(d, b, rtol=1e-12, max_iter=6)
     assert rc == dgmf.DG_NOT_CONVERGED and rep["iterations"] == 6
     assert abs(rep["true_rel_res"] - rep["rel_res"]) < 1e-10 * rep["rel_res"]
+
+
+@pytest.mark.parametrize("k,n_el,dtype", [
+    (3, (57, 57, 56), torch.float32), (7, (19, 18, 18), torch.float32), (7, (29, 28, 28), torch.float32),
+    (9, (12, 12, 11), torch.float64), (9, (20, 20, 20), torch.float64), (1, (67, 5, 3), torch.float32)])
+def test_both_sources_of_the_x_neighbours(k, n_el, dtype):
+    """Where the batch kernel's x-neighbours come from changes with the size at
+    n = 4 and 8 (FP32) and n = 10 (FP64): just inside each window of meshes
+    that load them all, and just above it, where those of the same batch come
+    from LDS (the other tests' small meshes lie below); n = 2 always loads.
+    Row ends inside a batch, batch ends and the wrap-around are sampled."""
+    msh = M.Mesh(n_el, (2.0, 1.7, 2.3))
+    u = inputs.uniform((msh.N, (k + 1) ** 3), seed=470 + k)
+    if dtype == torch.float32:
+        u = round_f32(u)
+    announce(f"laplace x-neighbours k={k} {dtype} n_el={n_el}")
+    y = _run(k, n_el, msh.length, u, dtype=dtype)
+    nx, ny, _ = n_el
+    E = max(1, 256 // (k + 1) ** 2)
+    rng = np.random.default_rng(17)
+    rows = nx * rng.integers(0, msh.N // nx, 40)
+    sample = np.unique(np.concatenate([rng.integers(0, msh.N, 100), rows, rows + nx - 1, [0, nx, nx * ny - 1, nx * ny],
+                                       np.minimum(np.arange(1, 9) * E, msh.N) - 1, [msh.N - 1]]))
+    ref = laplace_apply(u, k, msh, elems=sample)
+    assert rel_err(y[sample], ref) < (1e-12 if dtype == torch.float64 else 1e-5)
