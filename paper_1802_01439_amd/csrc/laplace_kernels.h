@@ -866,15 +866,7 @@ const LapTab<N, T>* lap_device_tab(const LaplacePlan& P, hipError_t* err) {
 }
 
 // The march kernel is built for FP64 up to n = 5 and for FP32 at n = 3 and 5
-// (the batch kernel is faster at every size elsewhere), and taken where input
-// and output together exceed 96 MB.  Below, the batch kernel's second reads of
-// neighbour pencils come from the caches, and its many short workgroups fill
-// the device better than few long marches; above, they come from memory, and
-// the march reads every column once.  Batch against march, us (bit-identical):
-// FP64 n = 5, 32^3 (66 MB) 20.1 / 24.6, 36^3 (93) 30.1 / 35.1, 40^3 (128)
-// 47.6 / 46.0, 51^3 (265) 98.3 / 94.1; n = 4, 44^3 (87) 24.0 / 27.2, 64^3 (268)
-// 81.9 / 71.6; n = 3, 48^3 (48) 15.6 / 16.7, 90^3 (315) 120 / 105; FP32 n = 5,
-// 40^3 (64) 24.6 / 26.9, 51^3 (133) 60.3 / 56.8; n = 3, 90^3 (157) 77.8 / 72.2.
+// (the batch kernel is faster at every size elsewhere).
 template <int N, typename T>
 constexpr bool lap_has_march() {
   return sizeof(T) == 8 ? N <= 5 : (N == 3 || N == 5);
@@ -915,29 +907,69 @@ bool lap_x_lds(const LaplacePlan& P) {
   return b <= lo || b > hi;
 }
 
+// Tiles x z segments x components of a march, about kLapMarchWGs workgroups.
+template <int N>
+LapWork lap_march_work(const LaplacePlan& P) {
+  using C = LapCfg<N>;
+  LapWork wk;
+  wk.ntx = (P.mesh.nx + C::TX - 1) / C::TX;
+  wk.nty = (P.mesh.ny + C::TY - 1) / C::TY;
+  const long tiles = (long)wk.ntx * wk.nty * P.n_comp;
+  const int want = (int)std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
+  wk.lz = (P.mesh.nz + want - 1) / want;
+  wk.nseg = (P.mesh.nz + wk.lz - 1) / wk.lz;
+  return wk;
+}
+
+// Whether a launch takes the march (bit-identical either way); plain: the
+// apply without a fused epilogue.  Times below: batch / march, us, three pairs
+// of input and output in turn.
+// Large meshes: the batch kernel's second reads of neighbour pencils come from
+// memory, and the march reads every column once.  Below, they come from the
+// caches, and many short workgroups fill the device better than few long
+// marches.  FP64 n = 2, 90^3 (89 MB) 29.6 / 35.0; n = 3, 59^3 (85) 26.4 / 28.0,
+// 60^3 (89) 31.9 / 31.8, 48x88x53 (92) 34.1 / 33.2, 61^3 (93) 35.0 / 36.0;
+// n = 4, 45^3 (89) 27.5 / 30.1, 46^3 (95) 32.6 / 31.8; n = 5, 36^3 (89) 31.1 /
+// 34.5, 51^3 (265) 98 / 94; FP32 n = 3, 75^3 (87) 38.6 / 40.5, 77^3 (94) 45.2 /
+// 44.8; n = 5, 43^3 (76) 28.8 / 29.2, 44^3 (81) 30.8 / 29.6, 49x67x29 (91) 39.9
+// / 35.9, but inside a Chebyshev CG solve, 44^3, 12.9 / 13.3 ms.
+// FP32 below that: the batch kernel's time grows evenly, the march's in steps
+// of one layer per workgroup, and it wins where its workgroups (8 resident per
+// CU at n = 3, 6 at n = 5) nearly fill one round of the device.  n = 3: 60^3
+// (four layers, 94 % of the round) 20.2 / 18.9, 68^3 (six, 91 %) 27.2 / 25.4,
+// 47^3 (two, 90 %) 12.2 / 11.9; but 46^3 (two, 85 %) 11.5 / 11.8, 57^3 (four,
+// 81 %) 17.9 / 18.7, and 69^3, just over one round, 28.2 / 29.6; in Chebyshev
+// CG solves 48^3 4.56 / 4.41 ms.  n = 5: 24^3 (90 %) 8.8 / 8.4, 35^3 (93 %) 18.1
+// / 17.6, but 30^3 (88 %) 12.6 / 13.2.  FP64 gains nothing there.
 // Planes that hold less than one full batch stay with the march: their batches
 // would be mostly empty, and a reduction's partials (one per workgroup) many.
 template <int N, typename T>
-bool lap_march(const LaplacePlan& P) {
+bool lap_march(const LaplacePlan& P, bool plain) {
   if constexpr (!lap_has_march<N, T>()) return false;
-  return lap_bytes<N, T>(P) > 96LL << 20 ||
-         (long long)P.mesh.nx * P.mesh.ny < LapCfgB<N>::E;
+  constexpr bool F32 = sizeof(T) == 4;
+  const bool small5 = F32 && N == 5 && plain;
+  const long long most = small5 ? 80 : N == 3 || N == 4 ? 92 : 96;   // MB
+  if ((long long)P.mesh.nx * P.mesh.ny < LapCfgB<N>::E || lap_bytes<N, T>(P) > most << 20) return true;
+  if (!small5 && !(F32 && N == 3)) return false;
+  constexpr long long round = 256 * (N == 3 ? 8 : 6);   // workgroups
+  const LapWork wk = lap_march_work<N>(P);
+  const long long grid = (long long)wk.ntx * wk.nty * wk.nseg * P.n_comp;
+  const long long need = N == 3 ? 80 * wk.lz + 15 : 89 * wk.lz;   // % of a layer of the round
+  return grid <= round && (N == 5 || wk.lz > 1) &&
+         100LL * P.n_comp * P.mesh.n_el >= need * round * LapCfg<N>::E;
 }
 
-// Workgroups of one launch (for the size of a partial-sum buffer).
+// Workgroups of one launch with a fused reduction (for the size of its
+// partial-sum buffer).
 template <int N, typename T>
 long lap_grid(const LaplacePlan& P) {
-  if (!lap_march<N, T>(P)) {
+  if (!lap_march<N, T>(P, false)) {
     using CB = LapCfgB<N>;
     const long PB = (P.mesh.nx * (long)P.mesh.ny + CB::E - 1) / CB::E;
     return PB * P.n_comp * P.mesh.nz;
   }
-  using C = LapCfg<N>;
-  const long ntx = (P.mesh.nx + C::TX - 1) / C::TX, nty = (P.mesh.ny + C::TY - 1) / C::TY;
-  const long tiles = ntx * nty * P.n_comp;
-  const long want = std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
-  const long lz = (P.mesh.nz + want - 1) / want;
-  return tiles * ((P.mesh.nz + lz - 1) / lz);
+  const LapWork wk = lap_march_work<N>(P);
+  return (long)wk.ntx * wk.nty * P.n_comp * wk.nseg;
 }
 
 // Launch y = A x through io.  tab: device table from lap_device_tab, or
@@ -950,20 +982,12 @@ hipError_t launch_laplace_io(const LaplacePlan& P, const IO& io, const LapTab<N,
     if (!tab) return err;
   }
   if constexpr (lap_has_march<N, T>()) {
-    if (lap_march<N, T>(P)) {
-      // tiles x z segments x components, about kLapMarchWGs workgroups
-      using C = LapCfg<N>;
-      LapWork wk;
-      wk.ntx = (P.mesh.nx + C::TX - 1) / C::TX;
-      wk.nty = (P.mesh.ny + C::TY - 1) / C::TY;
-      const long tiles = (long)wk.ntx * wk.nty * P.n_comp;
-      const int want = (int)std::max(1L, std::min<long>(P.mesh.nz, (kLapMarchWGs + tiles - 1) / tiles));
-      wk.lz = (P.mesh.nz + want - 1) / want;
-      wk.nseg = (P.mesh.nz + wk.lz - 1) / wk.lz;
-      const long grid = tiles * wk.nseg;
+    if (lap_march<N, T>(P, std::is_same<IO, LapPlainIO<T>>::value)) {
+      const LapWork wk = lap_march_work<N>(P);
+      const long grid = (long)wk.ntx * wk.nty * P.n_comp * wk.nseg;
       if (grid > 0x7fffffffL) return hipErrorInvalidConfiguration;
-      hipLaunchKernelGGL((laplace_march_kernel<N, T, IO>), dim3((unsigned)grid), dim3(C::THREADS), 0, stream, io,
-                         P.mesh, wk, tab);
+      hipLaunchKernelGGL((laplace_march_kernel<N, T, IO>), dim3((unsigned)grid), dim3(LapCfg<N>::THREADS), 0, stream,
+                         io, P.mesh, wk, tab);
       return hipGetLastError();
     }
   }

@@ -238,3 +238,37 @@ def test_both_sources_of_the_x_neighbours(k, n_el, dtype):
                                        np.minimum(np.arange(1, 9) * E, msh.N) - 1, [msh.N - 1]]))
     ref = laplace_apply(u, k, msh, elems=sample)
     assert rel_err(y[sample], ref) < (1e-12 if dtype == torch.float64 else 1e-5)
+
+
+@pytest.mark.parametrize("k,n_el,dtype", [
+    (1, (93, 92, 93), torch.float64), (2, (62, 61, 63), torch.float64), (3, (47, 46, 46), torch.float64),
+    (4, (37, 38, 37), torch.float64), (2, (78, 77, 79), torch.float32), (4, (47, 46, 48), torch.float32),
+    (2, (60, 59, 60), torch.float32), (2, (47, 47, 47), torch.float32), (4, (35, 35, 35), torch.float32),
+    (4, (24, 24, 24), torch.float32), (2, (57, 57, 57), torch.float32), (4, (36, 35, 35), torch.float32)])
+def test_march_tile_and_segment_borders(k, n_el, dtype):
+    """Meshes that take the marching kernel, with tiles that do not divide the
+    plane and a short last z segment: by their size (the first six) or, in
+    FP32, because its workgroups nearly fill one round of the device (the next
+    four); the last two just miss that.  Sampled elements at tile and segment
+    borders, corners and the wrap-around."""
+    msh = M.Mesh(n_el, (2.0, 1.7, 2.3))
+    u = inputs.uniform((msh.N, (k + 1) ** 3), seed=490 + k)
+    if dtype == torch.float32:
+        u = round_f32(u)
+    announce(f"laplace march borders k={k} {dtype} n_el={n_el}")
+    y = _run(k, n_el, msh.length, u, dtype=dtype)
+    rng = np.random.default_rng(19)
+    tx, ty = {1: (8, 8), 2: (7, 4), 3: (4, 4), 4: (5, 2)}[k]
+
+    def edge(n, step):   # both sides of up to four borders of a segmentation, the ends and some others
+        b = step * rng.integers(1, max(2, n // step + 1), 4)
+        v = np.concatenate([b - 1, b, [0, 1, n - 2, n - 1], rng.integers(0, n, 3)])
+        return np.unique(np.clip(v, 0, n - 1))
+
+    tiles = -(-n_el[0] // tx) * -(-n_el[1] // ty)
+    lz = -(-n_el[2] // max(1, min(n_el[2], -(-2048 // tiles))))
+    ex, ey, ez = edge(n_el[0], tx), edge(n_el[1], ty), edge(n_el[2], lz)
+    sample = np.unique((ex[:, None, None] + n_el[0] * (ey[None, :, None] + n_el[1] * ez[None, None, :])).ravel())
+    sample = np.sort(sample[rng.permutation(len(sample))[:400]])
+    ref = laplace_apply(u, k, msh, elems=sample)
+    assert rel_err(y[sample], ref) < (1e-12 if dtype == torch.float64 else 1e-5)
