@@ -212,3 +212,64 @@ def test_gmg_cg_estimates_level_bounds_and_counts_applies(cycle):
         q = outer - 2
         assert cyc == (q + 1) * per_cycle, r2
     assert it <= q <= it + 3, (it, q)
+
+
+def _cycle_of_operators(r, k, n_el, length, lam, degree, coarse_degree):
+    """The two-level V-cycle in FP64, composed on the device of the operators
+    that other tests compare with the oracle (Laplace apply, transfers)."""
+    def cheb(desc, dinv, b, deg, lmax):
+        theta, delta = 0.5 * (lmax + lmax / 20.0), 0.5 * (lmax - lmax / 20.0)
+        d = dinv * b / theta
+        x, rho = d.clone(), delta / theta
+        for _ in range(deg - 1):
+            new = 1.0 / (2.0 * theta / delta - rho)
+            d = new * rho * d + (2.0 * new / delta) * dinv * (b - dgmf.apply_laplace(desc, x))
+            x, rho = x + d, new
+        return x
+
+    fine, coarse = (dgmf.make_desc(k, n, length) for n in (n_el, tuple(m // 2 for m in n_el)))
+    df, dc = (torch.from_numpy(1.0 / dgmf.laplace_diagonal(d)).cuda() for d in (fine, coarse))
+    x = cheb(fine, df, r, degree, lam[0])
+    rc = dgmf.restrict(coarse, r - dgmf.apply_laplace(fine, x))
+    x = x + dgmf.prolongate(coarse, cheb(coarse, dc, rc, coarse_degree, lam[1]))
+    return x + cheb(fine, df, r - dgmf.apply_laplace(fine, x), degree, lam[0])
+
+
+@pytest.mark.parametrize("k,n_el,dtype,degree", [
+    (1, (94, 92, 92), torch.float64, 5), (2, (62, 62, 62), torch.float64, 4), (3, (48, 46, 46), torch.float64, 5),
+    (4, (38, 38, 38), torch.float64, 5), (4, (38, 38, 38), torch.float64, 3),
+    (2, (78, 78, 78), torch.float32, 5), (4, (48, 48, 46), torch.float32, 4),
+    (2, (60, 60, 60), torch.float32, 5), (2, (48, 48, 48), torch.float32, 6)])
+def test_vcycle_steps_on_the_marching_kernel(k, n_el, dtype, degree):
+    """A fine level that the marching kernel takes, several layers per
+    workgroup: the smoother's first, second, later (in place over the iterate
+    before) and added steps and the residuals, FP64 and FP32.  A cycle is a
+    sum of tens of operator applications, each good to rounding: FP64 1e-11,
+    FP32 1e-5, the tolerances of the parity tests above."""
+    length = tuple(0.1 * n for n in n_el)
+    lam = [2.0 * k + 2.0, 2.0 * k + 2.0]
+    g = torch.Generator(device="cuda").manual_seed(1150 + k)
+    r = (2 * torch.rand(n_el[0] * n_el[1] * n_el[2], (k + 1) ** 3, device="cuda", generator=g) - 1).to(dtype)
+    announce(f"V-cycle on the march k={k} n_el={n_el} {dtype} degree={degree}")
+    z = dgmf.gmg_vcycle(dgmf.make_desc(k, n_el, length), r, lam, degree=degree, coarse_degree=8).double()
+    ref = _cycle_of_operators(r.double(), k, n_el, length, lam, degree, 8)
+    # constants are in the operator's kernel: their rounding is not damped
+    z, ref = z - z.mean(), ref - ref.mean()
+    tol = 1e-11 if dtype == torch.float64 else 1e-5
+    assert float((z - ref).norm() / ref.norm()) < tol
+    assert float((z - ref).abs().max() / ref.abs().max()) < tol
+
+
+@pytest.mark.parametrize("degree,coarse", [(5, 30), (10, 30), (12, 61)])
+def test_vcycle_parity_f32_long_smoothing(degree, coarse):
+    # the smoother's step is the difference of two rounded iterates: its error
+    # must not grow with the number of steps (1e-5 as above)
+    k, n_el, levels = 3, (8, 8, 8), 3
+    fine = M.Mesh(n_el, (2 * np.pi,) * 3)
+    lam = _lams(k, fine, levels, 1.0, 1.0)
+    r = inputs.uniform((fine.N, (k + 1) ** 3), seed=1160 + coarse)
+    r = round_f32(r - r.mean())
+    announce(f"V-cycle FP32 degree={degree} coarse={coarse}")
+    d = dgmf.make_desc(k, n_el, (2 * np.pi,) * 3)
+    z = dgmf.gmg_vcycle(d, to_dev(r, torch.float32), lam, degree=degree, coarse_degree=coarse).double().cpu().numpy()
+    assert rel_err(z, vcycle(r, k, fine, levels, lam, degree=degree, coarse_degree=coarse)) < 1e-5
