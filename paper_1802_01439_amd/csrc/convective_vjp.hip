@@ -15,9 +15,10 @@
 // This file holds the one-pass kernel, organised like the convective kernel
 // (conv_common.h holds the even-odd tables and sweeps), the faces folded into
 // the cell sweeps, all of u and w in LDS at once.  It serves FP64 k = 1 and
-// FP32 k <= 3, where an element is too small for a wavefront per component;
-// above that the kernel of convective_vjp_split.hip is faster (measured
-// there).
+// FP32 k <= 3, where an element is too small for a wavefront per component,
+// and the meshes that just fit in one round of it (see vjp_onepass); elsewhere
+// from k = 2 (FP64) and k = 4 (FP32) on the kernel of convective_vjp_split.hip
+// is faster (measured there).
 //   P1  x sweeps from global memory: u -> S_x u; w -> S_x w and G_x w; the
 //       y/z neighbour layers of u and w -> S_x; the x-face layers -> S_y.
 //   P2  y sweeps in place: S_y S_x u, S_y S_x w (and G_y S_x w beside it),
@@ -573,14 +574,35 @@ static hipError_t launch_vjp_nq(const ConvPlan& P, const void* u, const void* w,
 
 int vjp_max_degree(bool) { return 11; }
 
+// Elements of one round of the one-pass kernel on the device's 256 CUs.
+template <int N, int Q, typename T>
+constexpr int vjp_round() {
+  using Sh = VjpShape1<N, Q, (int)sizeof(T)>;
+  return 256 * (160 * 1024 / (Sh::E * Sh::BYTES)) * Sh::E;
+}
+
+// Whether a launch takes the one-pass kernel.  FP64 k = 2 and FP32 k = 7 lie
+// close to the split kernel, and a mesh that the one-pass kernel finishes in
+// one round (its time is that of one workgroup until the round is full) is
+// faster here where the split kernel's workgroups already share the CUs.
+// Split against one-pass, us: FP64 k = 2 2000 elements 9.8 / 10.3, 2100 11.0 /
+// 10.8, 3072 12.2 / 11.1, 3094 13.4 / 16.9; FP32 k = 7 240 11.6 / 11.6, 288
+// 13.9 / 12.0, 500 14.4 / 12.3, 520 17.6 / 21.8.
+bool vjp_onepass(const ConvPlan& P, bool f32) {
+  const int n = P.mesh.n_el;
+  if (f32) return P.k <= 3 || (P.k == 7 && n > 256 && n <= vjp_round<8, 11, float>());
+  return P.k == 1 || (P.k == 2 && n > 2048 && n <= vjp_round<3, 4, double>());
+}
+
 hipError_t launch_convective_vjp(const ConvPlan& P, bool f32, const void* u, const void* w, void* g,
                                  hipStream_t s) {
-  if (P.k >= (f32 ? 4 : 2)) return launch_convective_vjp_split(P, f32, u, w, g, s);
-  if (!f32) return launch_vjp_nq<2, 2, double>(P, u, w, g, s);
+  if (!vjp_onepass(P, f32)) return launch_convective_vjp_split(P, f32, u, w, g, s);
+  if (!f32) return P.k == 1 ? launch_vjp_nq<2, 2, double>(P, u, w, g, s) : launch_vjp_nq<3, 4, double>(P, u, w, g, s);
   switch (P.k) {
     case 1: return launch_vjp_nq<2, 2, float>(P, u, w, g, s);
     case 2: return launch_vjp_nq<3, 4, float>(P, u, w, g, s);
-    default: return launch_vjp_nq<4, 5, float>(P, u, w, g, s);
+    case 3: return launch_vjp_nq<4, 5, float>(P, u, w, g, s);
+    default: return launch_vjp_nq<8, 11, float>(P, u, w, g, s);
   }
 }
 

@@ -128,6 +128,37 @@ def test_meshes_of_few_elements(k, n_el):
         assert rel_err(g.double().cpu().numpy(), ref) < tol
 
 
+@pytest.mark.parametrize("k,n_el,dtype", [
+    (2, (32, 8, 8), torch.float64), (2, (3, 683, 1), torch.float64), (2, (16, 16, 12), torch.float64),
+    (2, (7, 439, 1), torch.float64), (7, (8, 8, 4), torch.float32), (7, (257, 1, 1), torch.float32),
+    (7, (8, 8, 8), torch.float32), (7, (27, 19, 1), torch.float32)])
+def test_meshes_of_one_round_of_the_one_pass_kernel(k, n_el, dtype):
+    """Both kernels at the ends of the element counts that go to the one-pass
+    one (FP64 k = 2: 2049 to 3072, FP32 k = 7: 257 to 512): the last mesh
+    below, the first and the last inside, the first above.  FP32 against the
+    FP64 kernel, FP64 against the oracle on a few elements, each the centre of
+    the 3^3 mesh of its surroundings.  Tolerances of this file."""
+    msh = M.Mesh(n_el, tuple(0.3 * n for n in n_el))
+    n3 = (k + 1) ** 3
+    u = round_f32(inputs.uniform((3, msh.N, n3), seed=1800 + k))
+    w = round_f32(inputs.uniform(u.shape, seed=1900 + k))
+    announce(f"vjp one round k={k} {dtype} n_el={n_el}")
+    d = dgmf.make_desc(k, n_el, msh.length, lf_factor=0.6)
+    g = dgmf.vjp_convective(d, to_dev(u, dtype), to_dev(w, dtype)).double().cpu().numpy()
+    if dtype == torch.float32:
+        ref = dgmf.vjp_convective(d, to_dev(u), to_dev(w)).cpu().numpy()
+        assert rel_err(g, ref) < 1e-5
+        return
+    block = M.Mesh((3, 3, 3), (0.9,) * 3)
+    nx, ny, nz = n_el
+    o = np.arange(-1, 2)
+    for e in (0, nx - 1, nx * ny * (nz // 2) + nx // 2, msh.N // 3, msh.N - 1):
+        ex, ey, ez = e % nx, e // nx % ny, e // (nx * ny)
+        around = ((ex + o) % nx + nx * ((ey + o[:, None]) % ny + ny * ((ez + o[:, None, None]) % nz))).ravel()
+        ref = convective_vjp(u[:, around], w[:, around], k, block, lf_factor=0.6)[:, 13]
+        assert rel_err(g[:, e], ref) < 1e-12
+
+
 def test_exact_ties_follow_half_half_convention():
     k = 2
     msh = M.cube(2)
