@@ -36,7 +36,7 @@ template <int NQ>
 __global__ void __launch_bounds__(kSumThreads) k_finalize(const double* __restrict__ partial, int nblocks,
                                                           double* __restrict__ out) {
   double v[NQ];
-  block_sums<NQ>(partial, nblocks, v);
+  block_sums<kSumThreads, NQ>(partial, nblocks, v);
   if (threadIdx.x != 0) return;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) out[q] = v[q];
@@ -166,10 +166,11 @@ __global__ void __launch_bounds__(kThreads) k_fill(double* __restrict__ y, doubl
 // unprojected; every use subtracts mu.
 
 // alpha = rz / p.q  (p.q from one partial), breakdown if p.q <= 0 or not finite
-__global__ void __launch_bounds__(kSumThreads) k_fin_alpha(const double* __restrict__ partial, int nblocks,
-                                                        double* __restrict__ st) {
+template <int TH>
+__global__ void __launch_bounds__(TH) k_fin_alpha(const double* __restrict__ partial, int nblocks,
+                                                  double* __restrict__ st) {
   double v[1];
-  block_sums<1>(partial, nblocks, v);
+  block_sums<TH, 1>(partial, nblocks, v);
   const double pq = v[0];
   if (threadIdx.x != 0) return;
   if (st[kDone] != 0.0) {
@@ -230,9 +231,9 @@ __device__ void account(double* st, double rn2, double rz, bool start) {
 // Jacobi: scalars of the new residual (sums from k_update_r_st<true>);
 // beta = rz_new / rz (a fixed symmetric preconditioner: standard PCG)
 __global__ void __launch_bounds__(kSumThreads) k_fin_jacobi(const double* __restrict__ partial, int nblocks,
-                                                         double* __restrict__ st, int start) {
+                                                            double* __restrict__ st, int start) {
   double v[4];
-  block_sums<4>(partial, nblocks, v);
+  block_sums<kSumThreads, 4>(partial, nblocks, v);
   const double Sr = v[0], Srr = v[1], Sdr = v[2], Srdr = v[3];
   if (threadIdx.x != 0) return;
   if (!start && st[kDone] != 0.0) return;
@@ -253,9 +254,9 @@ __global__ void __launch_bounds__(kSumThreads) k_fin_jacobi(const double* __rest
 
 // Chebyshev: mean and norm of the new residual (sums from k_update_r_st<false>)
 __global__ void __launch_bounds__(kSumThreads) k_fin_resid(const double* __restrict__ partial, int nblocks,
-                                                        double* __restrict__ st, int start) {
+                                                           double* __restrict__ st, int start) {
   double v[2];
-  block_sums<2>(partial, nblocks, v);
+  block_sums<kSumThreads, 2>(partial, nblocks, v);
   const double Sr = v[0], Srr = v[1];
   if (threadIdx.x != 0) return;
   if (!start && st[kDone] != 0.0) return;
@@ -307,10 +308,11 @@ __global__ void __launch_bounds__(kThreads) k_fill32(float* __restrict__ y, floa
 }
 
 // flexible beta = r'.(z' - zold) / rz with z' = z - mu_z
-__global__ void __launch_bounds__(kSumThreads) k_fin_cheb(const double* __restrict__ partial, int nblocks,
-                                                       double* __restrict__ st, int start) {
+template <int TH>
+__global__ void __launch_bounds__(TH) k_fin_cheb(const double* __restrict__ partial, int nblocks,
+                                                 double* __restrict__ st, int start) {
   double v[3];
-  block_sums<3>(partial, nblocks, v);
+  block_sums<TH, 3>(partial, nblocks, v);
   const double Sz = v[0], Srz = v[1], Srzo = v[2];
   if (threadIdx.x != 0) return;
   if (!start && st[kDone] != 0.0) return;
@@ -422,7 +424,10 @@ hipError_t cg_state_init(double* st, double tol2, int max_it, double sum_d, long
   return hipGetLastError();
 }
 hipError_t cg_fin_alpha(const double* partial, int nblocks, double* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st);
+  if (nblocks > kManySums)
+    hipLaunchKernelGGL(k_fin_alpha<kManySumThreads>, dim3(1), dim3(kManySumThreads), 0, s, partial, nblocks, st);
+  else
+    hipLaunchKernelGGL(k_fin_alpha<kSumThreads>, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st);
   return hipGetLastError();
 }
 hipError_t cg_update_r_st(double* r, const double* q, const double* dinv, int n3, const double* st, bool jacobi,
@@ -440,7 +445,11 @@ hipError_t cg_fin_resid(const double* partial, double* st, bool start, hipStream
   return hipGetLastError();
 }
 hipError_t cg_fin_cheb(const double* partial, int nblocks, double* st, bool start, hipStream_t s) {
-  hipLaunchKernelGGL(k_fin_cheb, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st, start ? 1 : 0);
+  if (nblocks > kManySums)
+    hipLaunchKernelGGL(k_fin_cheb<kManySumThreads>, dim3(1), dim3(kManySumThreads), 0, s, partial, nblocks, st,
+                       start ? 1 : 0);
+  else
+    hipLaunchKernelGGL(k_fin_cheb<kSumThreads>, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st, start ? 1 : 0);
   return hipGetLastError();
 }
 hipError_t cg_cheb1(const double* r, float* z, const float* zprev, const float* dinv32, int n3, const double* st,

@@ -51,34 +51,38 @@ __device__ __forceinline__ void step_xp(double* __restrict__ x, double* __restri
   }
 }
 
-// One workgroup on an idle device: bound by the latency of its loads, so 16
-// wavefronts with four loads (or pairs) in flight each (256 threads in a plain loop took
-// 25.9 us for the 2 x 10368 partials of a dual-splitting velocity solve at
-// k = 7, 24^3, this takes 6 us).
-constexpr int kSumThreads = 1024;
+// Threads of a final sum.  One workgroup on an idle device, bound by the
+// latency of its loads: four in flight per thread and quantity (two for three
+// and more quantities in 1024 threads, for the registers), and 16 wavefronts only
+// for many partials, since they cost more to start and to combine.  256 against
+// 1024 threads, us: four quantities of 1024 partials 2.7 / 5.0, three 2.3 / 4.1,
+// two 2.1 / 3.3; one of 4096 2.8 / 2.3, three 3.5 / 4.6; two of 10368 (a
+// dual-splitting velocity solve, k = 7, 24^3) 5.8 / 5.2, of 30000 13.7 / 10.4
+// (256 threads in a plain loop: 1024 partials 2.1-3.2, 10368 12.7).
+constexpr int kSumThreads = 256, kManySumThreads = 1024, kManySums = 4096;
 
 // Sums of partial[q * nblocks + i] over i for q < NQ, in a fixed order
 // (thread-strided, then across the wavefront, then across the wavefronts);
 // valid in thread 0.
-template <int NQ>
+template <int TH, int NQ>
 __device__ __forceinline__ void block_sums(const double* __restrict__ partial, int nblocks, double (&out)[NQ]) {
-  constexpr int W = kSumThreads / 64, U = NQ > 2 ? 2 : 4;
+  constexpr int W = TH / 64, U = TH == kManySumThreads && NQ > 2 ? 2 : 4;
   __shared__ double sh[NQ][W];
   double s[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) s[q] = 0.0;
-  for (int i0 = threadIdx.x; i0 < nblocks; i0 += U * kSumThreads) {
+  for (int i0 = threadIdx.x; i0 < nblocks; i0 += U * TH) {
     double v[U][NQ];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = min(i0 + u * kSumThreads, nblocks - 1);
+      const int i = min(i0 + u * TH, nblocks - 1);
 #pragma unroll
       for (int q = 0; q < NQ; ++q) v[u][q] = partial[(size_t)q * nblocks + i];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) s[q] += i0 + u * kSumThreads < nblocks ? v[u][q] : 0.0;
+      for (int q = 0; q < NQ; ++q) s[q] += i0 + u * TH < nblocks ? v[u][q] : 0.0;
     }
   }
 #pragma unroll

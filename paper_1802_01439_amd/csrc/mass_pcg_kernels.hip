@@ -16,7 +16,7 @@ constexpr int kThreads = kCgThreads;
 __global__ void __launch_bounds__(kSumThreads) k_mp_start(const double* __restrict__ partial, int nblocks,
                                                           double* __restrict__ st) {
   double v[1];
-  block_sums<1>(partial, nblocks, v);
+  block_sums<kSumThreads, 1>(partial, nblocks, v);
   const double rz = v[0];
   if (threadIdx.x != 0) return;
   st[kRZ] = rz;
@@ -28,10 +28,11 @@ __global__ void __launch_bounds__(kSumThreads) k_mp_start(const double* __restri
 
 // after the r update and z = M^-1 r, with their partials r.r and r.z:
 // convergence test, iteration count, beta
-__global__ void __launch_bounds__(kSumThreads) k_mp_beta(const double* __restrict__ partial, int nblocks,
-                                                         double* __restrict__ st) {
+template <int TH>
+__global__ void __launch_bounds__(TH) k_mp_beta(const double* __restrict__ partial, int nblocks,
+                                                double* __restrict__ st) {
   double v[2];
-  block_sums<2>(partial, nblocks, v);
+  block_sums<TH, 2>(partial, nblocks, v);
   const double rr = v[0], rz = v[1];
   if (threadIdx.x != 0) return;
   if (st[kDone] != 0.0) {
@@ -78,7 +79,10 @@ hipError_t mpcg_start(const double* partial, double* st, hipStream_t s) {
 }
 
 hipError_t mpcg_beta(const double* partial, int nblocks, double* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_mp_beta, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st);
+  if (nblocks > kManySums)
+    hipLaunchKernelGGL(k_mp_beta<kManySumThreads>, dim3(1), dim3(kManySumThreads), 0, s, partial, nblocks, st);
+  else
+    hipLaunchKernelGGL(k_mp_beta<kSumThreads>, dim3(1), dim3(kSumThreads), 0, s, partial, nblocks, st);
   return hipGetLastError();
 }
 

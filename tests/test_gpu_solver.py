@@ -225,3 +225,20 @@ def test_lambda_max_against_dense_eigenvalues(k, N):
     _, rep, _ = dgmf.cg_solve(dgmf.make_desc(k, N), to_dev(b), precond=dgmf.DG_PC_CHEB_F32, max_iter=1)
     ratio = rep["lambda_max"] / (1.1 * lam_true)
     assert 1.0 - 2e-3 <= ratio <= 1.0 + 1e-9, (rep["lambda_max"], lam_true)
+
+
+@pytest.mark.parametrize("precond", [dgmf.DG_PC_JACOBI_F64, dgmf.DG_PC_CHEB_F32])
+@pytest.mark.parametrize("n_el", [(16, 16, 16), (17, 241, 1), (3, 1, 1)])
+def test_final_sums_around_the_change_of_their_workgroup(n_el, precond):
+    """One partial sum per element at k = 11: 4096 of them (the most that 256
+    threads add), 4097 (1024 threads) and 3.  A wrong sum gives a wrong step
+    length or direction: the recurrence's residual is the true one, and falls."""
+    d = dgmf.make_desc(11, n_el, tuple(0.1 * n for n in n_el))
+    g = torch.Generator(device="cuda").manual_seed(4)
+    b = 2 * torch.rand(n_el[0] * n_el[1] * n_el[2], 1728, device="cuda", dtype=torch.float64, generator=g) - 1
+    announce(f"CG final sums n_el={n_el} precond={precond}")
+    _, two, rc = dgmf.cg_solve(d, b, precond=precond, rtol=1e-12, max_iter=2)
+    _, rep, rc = dgmf.cg_solve(d, b, precond=precond, rtol=1e-12, max_iter=40)
+    assert rc == dgmf.DG_OK or rep["iterations"] == 40   # three elements may converge before
+    assert abs(rep["true_rel_res"] - rep["rel_res"]) < 1e-10 * max(1.0, rep["rel_res"])
+    assert rep["rel_res"] < 0.9 * two["rel_res"]
