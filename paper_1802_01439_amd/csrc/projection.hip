@@ -14,13 +14,14 @@
 // on the face layer (LGL face nodes, M1 the 1D mass on [0,1]).
 //
 // Component j is swept along its two tangential directions first and along
-// e_j last.  The one-sided traces on the faces normal to e_j, which the
-// continuity term needs at the tangential Gauss points, are then the pencil's
-// end values; the neighbours' traces come from the same two sweeps over their
-// facing layers.  With M1 = S^T W S the term area {tau_C} W (u^-_j - u^+_j) is
-// added after the S^T sweep along e_j, and the two tangential S^T sweeps
-// finish it: no face mass products.  Along e_j, S and Dg (and Dg^T and S^T)
-// run on one pencil in registers.
+// e_j last.  The same two sweeps over the jumps u^-_j - u^+_j of the nodes on
+// the two faces normal to e_j give the jumps at the tangential Gauss points.
+// With M1 = S^T W S the term area {tau_C} W (u^-_j - u^+_j) is added after the
+// S^T sweep along e_j, and the two tangential S^T sweeps finish it: no face
+// mass products.  Along e_j, S and Dg (and Dg^T and S^T) run on one pencil in
+// registers.  The jumps are formed at the nodes, from the loaded values: as
+// the difference of two swept traces a small jump would carry the rounding of
+// the traces, which strong penalties multiply.
 //
 // Mapping: one workgroup per batch of E elements, n^2 threads per component
 // (one per pencil); batches are mapped XCD-aware, so that the neighbours'
@@ -33,10 +34,12 @@
 //
 // What bounds it: vector instructions (55-75 % of the cycles issue one) and
 // LDS (35-45 %) together; memory sees each value read and written once.
-// Measured, FP64, against sweeps in the order x, y, z for all components with
-// the face terms from two products with M1: k = 3, 32^3 43.0 -> 35.0 us,
-// k = 6, 19x18x17 42.3 -> 31.8, k = 7, 24^3 130 -> 95, k = 9, 16^3 114 -> 69,
-// k = 11, 12^3 68 -> 53; FP32 k = 7, 24^3 70 -> 57.
+// Measured with three sets of vectors in turn, FP64, against sweeps in the
+// order x, y, z for all components with the face terms from two products with
+// M1: k = 3, 32^3 45.9 -> 37.7 us, k = 6, 19x18x17 44.5 -> 34.9, k = 7, 24^3
+// 124 -> 95, k = 9, 16^3 113 -> 72, k = 11, 12^3 68 -> 54; FP32 k = 7, 24^3
+// 66 -> 56.  Jumps of swept traces instead of swept jumps would take 5 % less
+// at k = 6 and 4 % at k = 11, the same elsewhere.
 #include <algorithm>
 #include <cmath>
 
@@ -100,7 +103,7 @@ struct ProjTab {
 
 // LDS layout of one element.  Every component j keeps its block by role: t2
 // innermost, then t1, then the direction n normal to its faces (e_j), with the
-// neighbours' facing layers at both ends (n + 2 layers).  t1 is the first
+// jumps to the neighbours' facing layers at both ends (n + 2 layers).  t1 is the first
 // tangential direction swept (z; y for j = 2), t2 the second (x; y for j = 0).
 // So the sweeps run at strides known at compile time, and an odd stride of t1
 // keeps them nearly free of bank conflicts.  Then the six face factors.
@@ -108,12 +111,12 @@ template <int N>
 struct ProjCfg {
   static constexpr int N2 = N * N, N3 = N * N * N, M = N + 2;
   // The first two sweeps cover n + 2 layers: n^2 threads per component take
-  // their own layers and then, 2 n of them, the neighbours' two; or n (n + 2)
-  // threads take one pencil each.  The second way costs another wavefront at
-  // most n (n = 8: 4 instead of 3), which measured slower up to n = 10 (n = 6
-  // 111 against 105 us at 32^3, n = 8 98 / 95 at 24^3, n = 9 51 / 45 at 16^3),
-  // but none at n = 7 (31.8 / 33.1), and for n = 11, 12 it is one in eight
-  // (68 / 74, 53 / 56).
+  // their own layers, and those with a pencil on a face its jump too (of the
+  // values they have loaded); or n (n + 2) threads take one pencil each.  The
+  // second way costs another wavefront at most n (n = 8: 4 instead of 3), which
+  // measured slower up to n = 10 (n = 6 120 against 104 us at 32^3, n = 8 102 /
+  // 95 at 24^3, n = 9 55 / 45 at 16^3), but none at n = 7 (34.9 / 35.3), and for
+  // n = 11, 12 it is one in eight (54 / 60, 54 / 56).
   static constexpr bool TWO = N <= 10 && N != 7;
   static constexpr int TC = TWO ? N2 : N * M;
   // elements per workgroup: full wavefronts, and no more of them than needed
@@ -145,13 +148,16 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
     const int e = e0 + le;
     const bool active = e < mesh.n_el;
     T* A = lds + le * C::PER + j * C::CP;
-    // layer q of element src, which is its layer lay: S along t1 at position t of t2
-    auto sweep1 = [&](int q, int t, int src, int lay) {
-      const T* g = u + j * cs + (size_t)src * N3 + pick(j, lay + N * t, t + N * lay, t + N2 * lay);
+    // pencil t of layer lay of element el, along t1
+    auto load = [&](int el, int lay, int t, T (&x)[N]) {
+      const T* g = u + j * cs + (size_t)el * N3 + pick(j, lay + N * t, t + N * lay, t + N2 * lay);
       const int gs = j == 2 ? N : N2;
-      T x[N], v[N];
 #pragma unroll
       for (int c = 0; c < N; ++c) x[c] = g[gs * c];
+    };
+    // S along t1 of a pencil into position t of layer q
+    auto sweep1 = [&](int q, int t, const T (&x)[N]) {
+      T v[N];
       eo_apply<N, 1>(fresh(tab)->S, x, v);
       T* a = A + SN * q + t;
 #pragma unroll
@@ -179,14 +185,30 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
       };
       if constexpr (C::TWO) {
         const int a = p % N, b = p / N;   // lanes run along x first
-        sweep1(1 + (j == 0 ? a : b), j == 0 ? b : a, e, j == 0 ? a : b);
-        if (p < 2 * N) {
-          sweep1(b ? M - 1 : 0, a, b ? nr : nl, b ? 0 : N - 1);
-          if (a == 0) factor(b);
+        const int lay = j == 0 ? a : b, t = j == 0 ? b : a;
+        const bool edge = lay == 0 || lay == N - 1;
+        T x[N], h[N];
+        load(e, lay, t, x);
+        if (edge) {
+          load(lay ? nr : nl, N - 1 - lay, t, h);
+          if (t == 0) factor(lay != 0);
+#pragma unroll
+          for (int c = 0; c < N; ++c) h[c] = x[c] - h[c];
         }
+        sweep1(1 + lay, t, x);
+        if (edge) sweep1(lay ? M - 1 : 0, t, h);
       } else {
         const int q = j == 0 ? p % M : p / N, t = j == 0 ? p / M : p % N;
-        sweep1(q, t, q == 0 ? nl : q == M - 1 ? nr : e, q == 0 ? N - 1 : q == M - 1 ? 0 : q - 1);
+        const bool jump = q == 0 || q == M - 1;
+        const int lay = q == 0 ? 0 : q == M - 1 ? N - 1 : q - 1;
+        T x[N], h[N];
+        load(e, lay, t, x);
+        if (jump) {
+          load(q ? nr : nl, N - 1 - lay, t, h);
+#pragma unroll
+          for (int c = 0; c < N; ++c) x[c] -= h[c];
+        }
+        sweep1(q, t, x);
         if (t == 0 && (q == 0 || q == M - 1)) factor(q != 0);
       }
     }
@@ -209,7 +231,7 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
   const bool active = tid < E * 3 * N2 && e < mesh.n_el;
   T* L = lds + le * C::PER;
   T* A = L + j * C::CP;
-  T* aj = A + p0 + S1 * p1;   // (t2, t1) = (p0, p1), from the left neighbour's layer on
+  T* aj = A + p0 + S1 * p1;   // (t2, t1) = (p0, p1), from the jumps of the left face on
   // ---- P2: S along e_j; keep vol W ug_j and the face terms in registers;
   //      the derivative (1/h_j) Dg_j ug_j goes back
   T mw[N], f0 = 0, f1 = 0;
@@ -219,8 +241,8 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
 #pragma unroll
     for (int r = 0; r < N; ++r) x[r] = aj[SN * (r + 1)];
     const T w2 = t.w[p0] * t.w[p1];   // tensor weight of the two fixed indices
-    f0 = L[C::FC + 2 * j] * w2 * (x[0] - aj[0]);
-    f1 = L[C::FC + 2 * j + 1] * w2 * (x[N - 1] - aj[SN * (N + 1)]);
+    f0 = L[C::FC + 2 * j] * w2 * aj[0];
+    f1 = L[C::FC + 2 * j + 1] * w2 * aj[SN * (N + 1)];
     eo_apply<N, 1>(t.S, x, v);
     const T wv = t.vol * w2;
 #pragma unroll

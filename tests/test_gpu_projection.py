@@ -80,6 +80,28 @@ def test_projection_batch_fills_and_strong_penalties(k, n_el, dtype):
     assert rel_err(y, projection_apply(u, k, msh, td, tc)) < (1e-12 if dtype == torch.float64 else 1e-5)
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("k", list(range(1, 12)))
+def test_projection_small_jumps_under_strong_penalties(k, dtype):
+    """A constant field with small jumps, and continuity penalties that bring
+    them up to its size (as the penalty is for a nearly conforming velocity):
+    the jumps must keep their own relative precision, not that of the field.
+    Reference: the constant part has no jump, so its share is the mass matrix
+    alone.  Tolerances of this file: FP64 1e-12, FP32 1e-5."""
+    n_el = (3, 2, 2)
+    msh = M.Mesh(n_el, (1.2, 1.0, 0.9))
+    size = 2.0 ** -17 if dtype == torch.float64 else 2.0 ** -10
+    const = np.array([1.0, -0.5, 0.75])[:, None, None]
+    u = round_f32(const + size * inputs.uniform((3, msh.N, (k + 1) ** 3), seed=910 + k))
+    v = u - const   # exact: u and const differ by less than const / 2
+    td = np.zeros(msh.N)
+    tc = round_f32(inputs.uniform((msh.N,), seed=920 + k, lo=0.5, hi=1.0) * float(np.min(msh.h)) / size)
+    announce(f"projection small jumps k={k} {dtype}")
+    y = _run(k, msh, u, td, tc, dtype)
+    ref = mass_apply(np.broadcast_to(const, u.shape), k, msh) + projection_apply(v, k, msh, td, tc)
+    assert rel_err(y, ref) < (1e-12 if dtype == torch.float64 else 1e-5)
+
+
 @pytest.mark.parametrize("k", [3, 8])
 def test_projection_zero_penalty_is_the_mass_matrix(k):
     msh, u, _, _ = _case(k, (4, 3, 2), (2.0, 1.5, 1.0), 850 + k, torch.float64)
