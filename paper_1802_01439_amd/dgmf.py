@@ -208,7 +208,7 @@ def _plain(first, shape, *others):
     shape) in others None or one of that shape on its device and of its dtype:
     all that _check_tensor and _placed ask, in one pass.  Where this is False
     the callers go through those two, which say what is wrong."""
-    if first.shape != shape or not first.is_cuda or not first.is_contiguous():
+    if first.shape != shape or not getattr(first, "is_cuda", False) or not first.is_contiguous():
         return False
     dtype, dev = first.dtype, first.get_device()
     for t, sh in others:
