@@ -859,12 +859,6 @@ LapTab<N, T> make_lap_tab(const LaplacePlan& P) {
   return t;
 }
 
-// Device copy of the plan's table (uploaded once per content and device).
-template <int N, typename T>
-const LapTab<N, T>* lap_device_tab(const LaplacePlan& P, hipError_t* err) {
-  return device_table_of("laplace", make_lap_tab<N, T>(P), err);
-}
-
 // The march kernel is built for FP64 up to n = 5 and for FP32 at n = 3 and 5
 // (the batch kernel is faster at every size elsewhere).
 template <int N, typename T>
@@ -972,8 +966,9 @@ long lap_grid(const LaplacePlan& P) {
   return (long)wk.ntx * wk.nty * P.n_comp * wk.nseg;
 }
 
-// Launch y = A x through io.  tab: device table from lap_device_tab, or
-// nullptr to take the plan's (looked up at its first launch).
+// Launch y = A x through io.  tab: a device copy of the table that the caller
+// has uploaded (lap_table_fill), or nullptr to take the plan's (looked up at
+// its first launch).
 template <int N, typename T, typename IO>
 hipError_t launch_laplace_io(const LaplacePlan& P, const IO& io, const LapTab<N, T>* tab, hipStream_t stream) {
   if (!tab) {

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
-#include <atomic>
 #include <vector>
 
 #include "common.h"
