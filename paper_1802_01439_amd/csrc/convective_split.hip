@@ -6,8 +6,9 @@
 // whole pencil of all three components needs 200 to 256 registers in FP64:
 // two wavefronts per SIMD, each with a serial chain of eleven phases, and the
 // vector ALU is busy 32-50 % of the time.  Here a thread holds one component
-// (m values) and one accumulator of n values at a time: 60 to 131 registers,
-// and no spills.  The back sweeps run in three passes over the flux direction
+// (m values) and one accumulator of n values at a time: 60 to 131 registers
+// and nothing spilled to memory (FP64 k = 10 holds 144 scalar registers of
+// table rows in vector lanes, k = 9 28, k = 11 21, k = 4, 6 and 8 two or three).  The back sweeps run in three passes over the flux direction
 // f, in each of which all three components' threads work, instead of in
 // three passes over the components.  The only thing the components exchange is
 // u_f at the Gauss points of the pass, F_jf = u_j u_f, through an LDS buffer
@@ -124,10 +125,11 @@ __device__ __forceinline__ decltype(auto) split_pick(const SplitTab<N, Q, T>& ct
 //   the neighbour face layers, which are dead by then.
 //  Face layers NB (neighbour) and FO (own, then the pencils' results), each
 //   y faces then z faces, [s][j][a][q], q = q3 (y faces) or q2 (z faces).
-//  Pitches of the face layers and of the column blocks: chosen with a model
-//  of the 32 8-byte banks over the access patterns of every phase (k = 5: a
-//  pitch of 9 instead of 8 and the pads below took the kernel from 563 to
-//  544 us; k = 10 from 878 to 827).
+//  Pitches of the face layers and of the column blocks: chosen by counting,
+//  for every phase, how many lanes of a half wavefront fall on each of the 32
+//  8-byte banks, over pitches m and m + 1 and pads up to 16 (k = 5: a pitch of 9
+//  instead of 8 and the pads below took the kernel from 563 to 544 us; k = 10
+//  from 878 to 827).
 template <int N, int Q, int SZ>
 struct SplitShape {
   static constexpr int N2 = N * N, N3 = N * N * N;
@@ -142,7 +144,8 @@ struct SplitShape {
   static constexpr int PER = FOo + 2 * FL;
   static constexpr int BYTES = PER * SZ;
   static constexpr int NW = (3 * Q * Q + 63) / 64, TH = NW * 64;
-  // one workgroup per CU: persistent form (FP64 k = 9 946 -> 857 us, k = 10
+  // one workgroup per CU (k = 9 needs 84.4 KB, 3 % too much for two; k = 10 and
+  // 11 119 and 143 KB): persistent form (FP64 k = 9 946 -> 857 us, k = 10
   // 820 -> 817, k = 11 763 -> 721).  Where more than one workgroup fits they
   // already hide each other's loads, and the registers of the loads in flight
   // cost a wavefront (k = 7 645 -> 736 us, FP32 k = 9 369 -> 415).

@@ -1,6 +1,7 @@
 // Vector-Jacobian product of the convective term (the form of
 // convective_vjp.hip) with one thread per pencil AND velocity component, in
-// passes over the derivative direction, FP64 k >= 2 and FP32 k >= 4.
+// passes over the derivative direction, FP64 k >= 2 and FP32 k >= 4 (but for
+// two ranges of mesh sizes, see vjp_onepass).
 //
 //   P_k = sum_d [ c_d u_d d_d w_k + delta_kd c_d sum_c u_c d_d w_c ],
 //
@@ -8,7 +9,9 @@
 // buffer that component d fills) and, for component d alone, the sum over the
 // components of u_c d_d w_c, which the other two send through LDS.  A thread
 // holds u_k and P_k at the m points and one pencil of n values: 64 to 143
-// registers in FP64.  The kernels this one replaces held all four swept fields
+// registers in FP64; k = 11, capped at 128 by its 14 wavefronts, spills 16 (68
+// bytes a lane), and k = 6, 8, 9, 10 hold 7 to 30 scalar registers of table rows
+// in vector lanes.  The kernels this one replaces held all four swept fields
 // of u and w at once: 43 KB of LDS per element at k = 4, 155 KB at k = 11,
 // where the registers spilled to memory (17 ms for 1.6e7 nodes).
 // Sweep and data layout as in convective_split.hip; written here for z first
@@ -101,7 +104,8 @@ __device__ __forceinline__ decltype(auto) vjp_pick(const VjpTab<N, Q, T>& ct, co
   const auto& t = vjp_pick<N, Q, T>(t##_ct, tab)
 
 // LDS layout of one element (units of T): slots, face layers and their
-// pitches as in convective_split.hip.  UB: c_d u_d of the pass; before that
+// pitches as in convective_split.hip, without that kernel's pads between the
+// layers (they were counted for its phases, not for these).  UB: c_d u_d of the pass; before that
 // (over the same space) the neighbour u layers and the w differences.
 // A pencil's m products (and two x-face terms) for component d go to its own
 // n+2 slots, which it has read by then, and m-n values beyond those: to extra

@@ -22,11 +22,10 @@
 // by three M sweeps: six 1D sweeps per element instead of the eight of the
 // unfactored form.
 //
-// GPU mapping, FP64 n <= 5 and FP32 n = 3, 5 on large meshes (see lap_march).
-// A workgroup owns an x-y tile
-// of TX x TY elements (n^2 threads per element) and marches through a segment
-// of consecutive z layers.  Every element column is loaded from global memory
-// once, one layer ahead: when a thread reaches layer ez it already holds its
+// GPU mapping, FP64 n <= 5 and FP32 n = 3, 5 on some meshes (see lap_march).
+// A workgroup owns an x-y tile of TX x TY elements (n^2 threads per element)
+// and marches through a segment of consecutive z layers.  Every element column
+// is loaded from global memory once, one layer ahead: when a thread reaches layer ez it already holds its
 // column of layer ez+1, whose end value and half slope are the z face data
 // above, while those of layer ez-1 were kept from the previous step.  x- and
 // y-neighbours inside the tile are read from LDS; only pencils across the
@@ -35,9 +34,9 @@
 // with pencils handed over through two LDS buffers (4 barriers).
 //
 // GPU mapping otherwise (measured: there the march's serial layer steps and
-// register pressure cost more than the neighbour loads it saves): one workgroup per batch of E = floor(256/n^2) consecutive
-// elements, batches walked strip by strip, XCD by XCD; each thread first
-// issues all of its global loads (own z column and the neighbour pencils,
+// register pressure cost more than the neighbour loads it saves): one
+// workgroup per batch of E = floor(256/n^2) consecutive elements, batches
+// walked strip by strip, XCD by XCD; each thread first issues all of its global loads (own z column and the neighbour pencils,
 // reduced at once to end values and slopes), then the same five phases.  What
 // bounds it is the address unit: waves wait for issue 60 % of their cycles
 // (VALU busy 39 %, LDS 32 % at FP64 k = 7), since an x-neighbour pencil per
@@ -878,8 +877,9 @@ long long lap_bytes(const LaplacePlan& P) {
 // 117.2).  While input and output stay in the caches it only moves loads into
 // the X phase, after the barrier: most degrees still gain 0-4 %, but FP32
 // n = 4 loses up to 5 % (47 MB 15.6 / 14.8), n = 8 3-5 % (75 MB 23.4 / 22.3;
-// 21 MB 10.3 / 10.4), FP64 n = 10, with two elements a batch, 3-8 % (64 MB
-// 32.5 / 30.0; 16 MB 13.0 / 13.7, 136 MB 62.3 / 62.8).  n = 2, whose pencil is
+// 21 MB 10.3 / 10.4), FP64 n = 10, with two elements a batch and 153 registers
+// against 122 (three wavefronts per SIMD against four), 3-8 % (64 MB 32.5 /
+// 30.0; 16 MB 13.0 / 13.7, 136 MB 62.3 / 62.8).  n = 2, whose pencil is
 // one 8-byte load, loses 2 % at every size.  The forms with a fused epilogue
 // move more vectors an entry: at n = 8 they are 0-0.3 % faster with LDS (a
 // V-cycle CG solve, 24^3, 10.04 / 10.07 ms), at n = 4 and 10 as the plain one

@@ -14,7 +14,17 @@
 // element's diagonal inverse, indexed by the local node.
 // Bound: HBM.  A smoothing of degree 5 moves 13 vectors (23 with the step
 // direction stored, x_1 written by a kernel of its own), the post-smoothing
-// with its residual 17 (26 before).
+// with its residual 17 (26 before).  The first step's two loads per neighbour
+// value cost registers (FP64 n = 9 195 against 140, two wavefronts per SIMD
+// instead of three; FP32 n = 9 108 / 72) and about a fifth of its own time, but
+// a whole cycle is faster at every degree, us: FP64 k = 1, 64^3 534 -> 444,
+// k = 4, 32^3 865 -> 665, k = 8, 16^3 824 -> 718, k = 11, 12^3 844 -> 767; FP32
+// 402 -> 374, 639 -> 557, 591 -> 522, 593 -> 520.
+// Rounding: the step x_j - x_{j-1} of two rounded iterates carries the rounding
+// of x, a stored direction that of its own size.  In FP32 cycles against FP64
+// ones the two forms are equally far off, also over many steps (medians of 16
+// inputs, k = 3: degrees 5 / 10 1.9e-7 both, 30 / 100 4.6e-7 stored, 4.4e-7
+// here; k = 7 1.3e-7, 3.8e-7 and 3.7e-7).
 #include "laplace_kernels.h"
 #include "ops.h"
 
