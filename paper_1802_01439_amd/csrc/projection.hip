@@ -36,10 +36,12 @@
 // LDS (35-45 %) together; memory sees each value read and written once.
 // Measured with three sets of vectors in turn, FP64, against sweeps in the
 // order x, y, z for all components with the face terms from two products with
-// M1: k = 3, 32^3 45.9 -> 37.7 us, k = 6, 19x18x17 44.5 -> 34.9, k = 7, 24^3
-// 124 -> 95, k = 9, 16^3 113 -> 72, k = 11, 12^3 68 -> 54; FP32 k = 7, 24^3
-// 66 -> 56.  Jumps of swept traces instead of swept jumps would take 5 % less
-// at k = 6 and 4 % at k = 11, the same elsewhere.
+// M1: k = 3, 32^3 45.9 -> 38.4 us, k = 6, 19x18x17 44.5 -> 34.3, k = 7, 24^3
+// 124 -> 94, k = 9, 16^3 113 -> 71, k = 11, 12^3 68 -> 54; FP32 k = 7, 24^3
+// 66 -> 56.  Jumps of swept traces instead of swept jumps would take 2-5 % less
+// at k = 6, where they are loaded apart, and the same or more elsewhere.  (For
+// k = 6, 10, 11: taking the own layers from LDS in the next phase instead of
+// loading them again was 0-6 % slower.)
 #include <algorithm>
 #include <cmath>
 
@@ -205,11 +207,11 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
         load(e, lay, t, x);
         if (jump) {
           load(q ? nr : nl, N - 1 - lay, t, h);
+          if (t == 0) factor(q != 0);
 #pragma unroll
           for (int c = 0; c < N; ++c) x[c] -= h[c];
         }
         sweep1(q, t, x);
-        if (t == 0 && (q == 0 || q == M - 1)) factor(q != 0);
       }
     }
     __syncthreads();
@@ -232,17 +234,15 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
   T* L = lds + le * C::PER;
   T* A = L + j * C::CP;
   T* aj = A + p0 + S1 * p1;   // (t2, t1) = (p0, p1), from the jumps of the left face on
-  // ---- P2: S along e_j; keep vol W ug_j and the face terms in registers;
-  //      the derivative (1/h_j) Dg_j ug_j goes back
-  T mw[N], f0 = 0, f1 = 0;
+  // ---- P2: S along e_j; keep vol W ug_j in registers; the derivative
+  //      (1/h_j) Dg_j ug_j goes back
+  T mw[N];
   if (active) {
     const auto& t = *fresh(tab);
     T x[N], v[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) x[r] = aj[SN * (r + 1)];
     const T w2 = t.w[p0] * t.w[p1];   // tensor weight of the two fixed indices
-    f0 = L[C::FC + 2 * j] * w2 * aj[0];
-    f1 = L[C::FC + 2 * j + 1] * w2 * aj[SN * (N + 1)];
     eo_apply<N, 1>(t.S, x, v);
     const T wv = t.vol * w2;
 #pragma unroll
@@ -265,15 +265,15 @@ projection_kernel(const T* __restrict__ u, T* __restrict__ y, const T* __restric
     };
     const T *a0 = block(0, SN, 1, S1), *a1 = block(1, 1, SN, S1), *a2 = block(2, 1, S1, SN);
     const int s0 = pick(j, SN, 1, S1), s1 = pick(j, 1, SN, S1), s2 = pick(j, 1, S1, SN);
-    const T td = tau_d[e] * t.vol * t.w[p0] * t.w[p1];
+    const T w2 = t.w[p0] * t.w[p1], td = tau_d[e] * t.vol * w2;
 #pragma unroll
     for (int q = 0; q < N; ++q) x[q] = td * t.w[q] * (a0[s0 * q] + a1[s1 * q] + a2[s2 * q]);
     eo_apply<N, -1>(t.Dt, x, v);
 #pragma unroll
     for (int r = 0; r < N; ++r) x[r] = fmadd(t.ih[j], v[r], mw[r]);
     eo_apply<N, 1>(t.St, x, v);
-    v[0] += f0;
-    v[N - 1] += f1;
+    v[0] += L[C::FC + 2 * j] * w2 * aj[0];
+    v[N - 1] += L[C::FC + 2 * j + 1] * w2 * aj[SN * (N + 1)];
 #pragma unroll
     for (int r = 0; r < N; ++r) mw[r] = v[r];
   }
