@@ -42,8 +42,9 @@
 //         8 367 -> 307, 9 406 -> 366, 10 433 -> 343, 11 430 -> 356
 // and on 16^3 elements, FP64 k = 5: 38 -> 32.  Below k = 4 the kernel of
 // convective.hip is faster (FP64 k = 3, 48^3: 240 against 247 us; FP32 142
-// against 156).  The vector ALU is now busy 40-80 % of the time (FP64; 32-50 %
-// before) resp. all the time (FP32), the LDS pipe 40-85 %.
+// against 156).  The vector ALU is now busy 43-75 % of the time (FP64; 32-50 %
+// before) resp. 92-100 % (FP32; four cycles per instruction), the LDS pipe
+// 28-58 % resp. 56-80 % (four cycles per instruction and the conflicts).
 #include <algorithm>
 #include <atomic>
 #include <cmath>

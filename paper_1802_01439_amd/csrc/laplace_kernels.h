@@ -38,10 +38,11 @@
 // workgroup per batch of E = floor(256/n^2) consecutive elements, batches
 // walked strip by strip, XCD by XCD; each thread first issues all of its global loads (own z column and the neighbour pencils,
 // reduced at once to end values and slopes), then the same five phases.  What
-// bounds it is the address unit: waves wait for issue 60 % of their cycles
-// (VALU busy 39 %, LDS 32 % at FP64 k = 7), since an x-neighbour pencil per
-// lane makes each load instruction touch 64 cache lines, and reading both
-// took as long as all other loads together.  x-neighbours in the same batch
+// bounds it is the address unit: waves wait for issue half of their cycles
+// (48 % at FP64 k = 7, where the vector ALU is 37 % busy; 60 % when both
+// x-neighbours came from memory): an x-neighbour pencil per lane makes each
+// load instruction touch 64 cache lines, and reading both took as long as all
+// other loads together.  x-neighbours in the same batch
 // are therefore read from LDS in the X phase; only pencils across a batch or
 // row end come from memory.  Degree-sweep meshes, us: FP64 k = 5 109 -> 98,
 // 6 118 -> 105, 7 95 -> 86, 8 101 -> 97; FP32 k = 6 69 -> 64, 7 51 -> 43,

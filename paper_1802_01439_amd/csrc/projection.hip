@@ -32,8 +32,9 @@
 // sweep runs in even-odd form, about half the multiply-adds of the dense
 // product.
 //
-// What bounds it: vector instructions (55-75 % of the cycles issue one) and
-// LDS (35-45 %) together; memory sees each value read and written once.
+// What bounds it: vector instructions (FP64 48-66 % of the time at four cycles
+// each, FP32 77-100 %) and LDS (23-40 % resp. 34-64 %, its conflicts with it)
+// together; memory sees each value read and written once.
 // Measured with three sets of vectors in turn, FP64, against sweeps in the
 // order x, y, z for all components with the face terms from two products with
 // M1: k = 3, 32^3 45.9 -> 38.4 us, k = 6, 19x18x17 44.5 -> 34.3, k = 7, 24^3
